@@ -8,16 +8,16 @@
 //     so the wave parallelises inside a placement: the lanes examine 64
 //     consecutive profile slots at once and a ballot gives the slots that
 //     would break the peak; the push-right then runs on that 64-bit mask in
-//     scalar registers.
+//     scalar registers. The default rules have a decoder of their own on the
+//     on-chip profile (decode_chip).
 //   * The power profile is one byte per time slot (Q_max <= 255) in LDS, next
 //     to the job order and per-job ready times of the chromosome. A decode
 //     whose schedule outgrows the on-chip slots is redone by an overflow
 //     kernel with the profile in global memory, sized by the instance's
 //     horizon bound, so no schedule is ever cut short.
 //   * Processing time and power of every (job, stage, machine) are packed in
-//     one 32-bit word (P | Q << 16); a placement reads its row through the
-//     scalar cache, and the earliest-completion machine choice runs on the
-//     scalar unit.
+//     one 32-bit word (pack_word), laid so that a start time plus the word is
+//     the key whose minimum is the earliest-completion machine.
 //   * The GA generation is one launch: each wave selects its two parents from
 //     the previous generation's objectives, builds its child (crossover,
 //     correction, mutation) in LDS, writes it out and decodes it. A second
@@ -41,6 +41,7 @@ typedef unsigned long long u64;
 typedef __attribute__((address_space(4))) const int32_t c_i32;
 typedef __attribute__((address_space(4))) const uint32_t c_u32;
 typedef __attribute__((address_space(4))) const int64_t c_i64;
+typedef __attribute__((address_space(3))) uint8_t lds_u8;
 
 // Workspace of ffs_decode_noalloc: one copy per GPU, held until the process
 // ends, shared by every such call on that GPU.
@@ -59,6 +60,10 @@ constexpr int kMaxTime = 1 << 27;    // completion times pack as (time << 4 | ma
 // (kNoMachine + p) << 4 | lane stays above every real key and below 2^32.
 constexpr int kNoMachine = 0x0FFF0000;
 static_assert(kNoMachine >= kMaxTime && kNoMachine + 0xFFFF < (1 << 28), "machine key");
+// The same for decode_chip, whose times stay below 2^17 (a ready or free time of at
+// most 65535 and one op).
+constexpr int kChipNoMachine = 1 << 18;
+static_assert(kChipNoMachine + 0xFFFF < (1 << 19), "machine key of 19 + 13 bits");
 
 // Device-side status word and small results at the head of every workspace.
 struct Header {
@@ -127,8 +132,20 @@ __device__ __forceinline__ u64 ballot64(bool p) { return __builtin_amdgcn_ballot
 // ---------------------------------------------------------------------------
 // Instance as the kernels see it.
 // ---------------------------------------------------------------------------
+// One word per (active job, stage, machine): P in bits 13-28 over the low 13 bits of
+// a machine key: the machine (4 bits), whether P exceeds the 64 slots the lanes hold
+// at once, and Q (8 bits). A start time << 13 plus the word is then the machine's
+// key, completion << 13 | machine << 9 | long << 8 | Q.
+constexpr int kKeyBits = 13;
+constexpr uint32_t kLongOp = 1u << 8;
+__host__ __device__ constexpr uint32_t pack_word(uint32_t p, uint32_t q, uint32_t m) {
+  return (p & 0xFFFFu) << kKeyBits | m << 9 | (p > 64 ? kLongOp : 0u) | (q & 0xFFu);
+}
+__device__ __forceinline__ int word_p(uint32_t w) { return (int)(w >> kKeyBits); }
+__device__ __forceinline__ int word_q(uint32_t w) { return (int)(w & 0xFFu); }
+
 struct DInst {
-  const uint32_t *pq;        // [n][g][omp]: P | Q << 16 of the active jobs, in gene order
+  const uint32_t *pq;        // [n][g][omp]: pack_word of the active jobs, in gene order
   const int32_t *due_k;      // [n]: due dates of the active jobs, in gene order
   const int32_t *nm;         // [g]
   const int32_t *due;        // [n_jobs]
@@ -314,7 +331,7 @@ enum : int { kDecOk = 0, kDecOverflow = 1, kDecInval = 2, kDecInfeasible = 3 };
 //                    (correction scratch before the decode)
 //   op    [n+2]      the current stage's ops in order, as 16-bit ranks (two spare
 //                    records that the op loop prefetches past the last)
-//   rec   [kRing]    packed P | Q << 16 rows of the stage's ops, one word per machine,
+//   rec   [kRing]    packed rows (pack_word) of the stage's ops, one word per machine,
 //                    staged from the packed table kWave / o_s ops at a time
 //   prof  [cap+64]   power in use per time slot after RS, one byte per slot (the last
 //                    64 stay zero so a chunk read never needs clamping)
@@ -322,14 +339,15 @@ enum : int { kDecOk = 0, kDecOverflow = 1, kDecInval = 2, kDecInfeasible = 3 };
 //                    at least n words): it is dead once the decode has built the ranks,
 //                    before the profile is cleared
 //
-// The hybrid GA's generation and init kernels, under the default decode rules,
-// use a narrow form of the same layout (`LdsN`): rdy in 16 bits, clamped to
-// [0, 65535] when loaded ([n+2] halfwords at the start, then jobs and op). A
-// time of 65535 or more exceeds every on-chip profile (at most 32 768 slots), so
-// such a decode overflows anyway, and an op's end is read only at the job's next
-// stage, after the stage's overflow check; 0 for a job ready before RS changes
-// no start (every use takes a max with a machine's free time, at least 0). A
-// decode redone off chip lays the wide form over the same allocation.
+// The default decode rules on at most kChipSlots on-chip slots (decode_chip) take
+// the chip form of the layout (`LdsN`): rdy in 16 bits, clamped to [0, 65535] when
+// loaded ([n+2] halfwords at the start, then jobs and op; a time past the slots
+// makes the decode overflow before it is read again, and 0 for a job ready before
+// RS changes no start: every use takes a max with a machine's free time, at least
+// 0) and by gene, op holds genes, rec [kChipChunk][MAXM], and the profile after 64
+// zero bytes and before 128 of 255, which breaks any peak: the 64 slots that end at
+// any completion are there to read, and a window that runs past the slots always
+// reads a 255. A decode redone off chip lays the wide form over the same allocation.
 template <class R>
 struct LdsT {
   int32_t *gene;
@@ -361,14 +379,22 @@ __host__ __device__ inline size_t lds_bytes(int n, int cap) {
   const size_t prof = cap > 0 ? align_up(cap, 16) + kWave : 0, gene = align_up((size_t)4 * n, 16);
   return lds_head(n) + (prof > gene ? prof : gene);
 }
-// The narrow form (LdsN), with room for the wide form of an off-chip redo.
-__host__ __device__ inline size_t lds_head_n(int n) {
-  return 3 * align_up((size_t)2 * n + 4, 16) + 4 * kRing;
+// The chip form (LdsN), with room for the wide form of an off-chip redo.
+constexpr int kChipSlots = 32768;
+constexpr int kChipChunk = 16;  // ops whose rows are staged at once
+__host__ __device__ inline size_t lds_head_n(int n, int omp) {
+  return 3 * align_up((size_t)2 * n + 4, 16) + 4 * kChipChunk * omp;
 }
-__host__ __device__ inline size_t lds_bytes_n(int n, int cap) {
-  const size_t prof = cap > 0 ? align_up(cap, 16) + kWave : 0, gene = align_up((size_t)4 * n, 16);
-  const size_t narrow = lds_head_n(n) + (prof > gene ? prof : gene), redo = lds_head(n) + gene;
-  return narrow > redo ? narrow : redo;
+__host__ __device__ inline size_t lds_bytes_n(int n, int omp, int cap) {
+  const size_t prof = (size_t)3 * kWave + cap, gene = align_up((size_t)4 * n, 16);
+  const size_t chip = lds_head_n(n, omp) + (prof > gene ? prof : gene);
+  const size_t redo = lds_head(n) + gene;
+  return chip > redo ? chip : redo;
+}
+// Whether decode_chip takes a decode: the default rules, and times past the slots
+// still apart from the free time of a lane without a machine.
+__host__ __device__ inline bool chip_rules(int rules, int cap) {
+  return rules == 0 && cap <= kChipSlots;
 }
 
 __device__ __forceinline__ Lds carve_lds(uint8_t *smem, int n) {
@@ -382,14 +408,14 @@ __device__ __forceinline__ Lds carve_lds(uint8_t *smem, int n) {
   l.gene = (int32_t *)l.prof;
   return l;
 }
-__device__ __forceinline__ LdsN carve_lds_n(uint8_t *smem, int n) {
+__device__ __forceinline__ LdsN carve_lds_n(uint8_t *smem, int n, int omp) {
   LdsN l;
   const size_t b = align_up((size_t)2 * n + 4, 16);
   l.rdy = (uint16_t *)smem;
   l.jobs = (uint16_t *)(smem + b);
   l.op = (uint16_t *)(smem + 2 * b);
   l.rec = (uint32_t *)(smem + 3 * b);
-  l.prof = (uint8_t *)l.rec + 4 * kRing;
+  l.prof = (uint8_t *)l.rec + 4 * kChipChunk * omp;
   l.gene = (int32_t *)l.prof;
   return l;
 }
@@ -419,6 +445,29 @@ __device__ __forceinline__ uint32_t machine_min_scalar(uint32_t v) {
                (uint32_t)__builtin_amdgcn_readlane((int)v, 7));
   }
   return (uint32_t)__builtin_amdgcn_readlane((int)machine_min<MAXM>(v), MAXM - 1);
+}
+
+// Minimum, or OR, over each group of MAXM neighbouring lanes, left in all of them
+// (quad permutes, then the half row and the row mirrored).
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xF, 0xF, true);
+}
+template <int MAXM>
+__device__ __forceinline__ uint32_t group_min(uint32_t v) {
+  v = min(v, dpp<0xB1>(v));
+  v = min(v, dpp<0x4E>(v));
+  if (MAXM > 4) v = min(v, dpp<0x141>(v));
+  if (MAXM > 8) v = min(v, dpp<0x140>(v));
+  return v;
+}
+template <int MAXM>
+__device__ __forceinline__ uint32_t group_or(uint32_t v) {
+  v |= dpp<0xB1>(v);
+  v |= dpp<0x4E>(v);
+  if (MAXM > 4) v |= dpp<0x141>(v);
+  if (MAXM > 8) v |= dpp<0x140>(v);
+  return v;
 }
 
 __device__ __forceinline__ int64_t wave_sum64(int64_t v) {
@@ -458,13 +507,10 @@ __device__ __forceinline__ bool live_at(const DInst &I, uint32_t jk, int s, bool
 //
 // RULES: false compiles the default rules only (no per-op rule test);
 // true reads I.rules (FFS_RULE_*). decode_core picks once per decode.
-template <int MAXM, bool PLAN, bool RULES, class L, class Prof>
-__device__ int decode_core_rules(const DInst &I, const L &l, Prof &&prof, int64_t *obj_out,
+template <int MAXM, bool PLAN, bool RULES, class Prof>
+__device__ int decode_core_rules(const DInst &I, const Lds &l, Prof &&prof, int64_t *obj_out,
                                  int64_t *work_out, int32_t *start_out, int32_t *mach_out,
                                  int32_t *span_max) {
-  using R = typename std::remove_pointer<decltype(l.rdy)>::type;
-  constexpr bool kNarrow = std::is_same<R, uint16_t>::value;
-  static_assert(!kNarrow || (!PLAN && !RULES), "narrow layout: default rules, no plan");
   const int lane = __lane_id();
   const int n = I.n;
   const u64 below = (1ull << lane) - 1;
@@ -488,8 +534,7 @@ __device__ int decode_core_rules(const DInst &I, const L &l, Prof &&prof, int64_
       const int j = ld_const(I.active, k);
       l.jobs[x] = (uint16_t)(k | min(ld_const(I.first, j), 15) << 12);
       // may be negative: every use takes a max with a machine's free time, at least 0
-      const int r = ld_const(I.ready, j) - rs;
-      l.rdy[x] = kNarrow ? (R)min(max(r, 0), 0xFFFF) : (R)r;
+      l.rdy[x] = ld_const(I.ready, j) - rs;
     }
   }
   if (ballot64(bad)) return kDecInval;
@@ -589,7 +634,7 @@ __device__ int decode_core_rules(const DInst &I, const L &l, Prof &&prof, int64_
     int vz;
     __asm__("v_mov_b32 %0, 0" : "=v"(vz));
     const uint16_t *opp = l.op + vz;
-    R *rdy_at = l.rdy + opp[0];  // the current op's job
+    int32_t *rdy_at = l.rdy + opp[0];  // the current op's job
     int rk1 = opp[1];                  // the next op's rank
     int ex = *rdy_at;                  // the current op's job's ready time
     // The stage's work sum, per lane (summed on the vector unit). Default rules:
@@ -618,14 +663,14 @@ __device__ int decode_core_rules(const DInst &I, const L &l, Prof &&prof, int64_
       opp += 1;
       recp += os;
       const int rk2 = opp[1];
-      R *const rdy_next = l.rdy + rk1;
+      int32_t *const rdy_next = l.rdy + rk1;
       const int ex_next = *rdy_next;
       const uint32_t pq_next = *recp;
       // the previous op's profile words, formed while this op's keys reduce
       const uint32_t cword = commit_word<typename std::decay<decltype(prof)>::type>(ct, cp, cq);
       // Machine of earliest completion (ties to the lowest index).
       const int t0v = max(ex, fr);  // earliest start on this lane's machine
-      const uint32_t key = ((uint32_t)(t0v + (int)(pqv & 0xFFFFu)) << 4) | (uint32_t)lane;
+      const uint32_t key = ((uint32_t)(t0v + word_p(pqv)) << 4) | (uint32_t)lane;
       uint32_t kmin = machine_min_scalar<MAXM>(key);
       int t = 0;
       StageWork cw = 0;
@@ -646,9 +691,9 @@ __device__ int decode_core_rules(const DInst &I, const L &l, Prof &&prof, int64_
           if (k >= 0 && m == first) continue;
           if ((uint32_t)__builtin_amdgcn_readlane((int)key, m) >= best) continue;
           const uint32_t pqm = (uint32_t)__builtin_amdgcn_readlane((int)pqv, m);
-          const int pm = (int)(pqm & 0xFFFFu);
+          const int pm = word_p(pqm);
           const int t0m = max(ox, __builtin_amdgcn_readlane(fr, m));
-          const int tm = prof.place(t0m, pm, (uint32_t)(I.q_max - (int)(pqm >> 16)));
+          const int tm = prof.place(t0m, pm, (uint32_t)(I.q_max - word_q(pqm)));
           cw += (StageWork)((tm - t0m) + pm);
           const uint32_t km = ((uint32_t)(tm + pm) << 4) | (uint32_t)m;
           if (km < best) {
@@ -660,7 +705,7 @@ __device__ int decode_core_rules(const DInst &I, const L &l, Prof &&prof, int64_
       }
       const int mb = (int)(kmin & 15u);
       const uint32_t pq = (uint32_t)__builtin_amdgcn_readlane((int)pqv, mb);
-      const int p = (int)(pq & 0xFFFFu), q = (int)(pq >> 16);
+      const int p = word_p(pq), q = word_q(pq);
       if (!power_ect) {
         // Q > Q_max is rejected by the instance checks; even then the unsigned
         // threshold only makes every slot pass, so the push-right still ends.
@@ -676,7 +721,7 @@ __device__ int decode_core_rules(const DInst &I, const L &l, Prof &&prof, int64_
       cq = q;
       const int end = t + p;
       fr = ffs_writelane(end, mb, fr);
-      *rdy_at = (R)(PLAN ? end | (mb << 27) : end);
+      *rdy_at = PLAN ? end | (mb << 27) : end;
       stage_work = stage_work + cw;
       rdy_at = rdy_next;
       rk1 = rk2;
@@ -700,7 +745,7 @@ __device__ int decode_core_rules(const DInst &I, const L &l, Prof &&prof, int64_
         const size_t gk = l.jobs[x] & 0xFFF, j = (size_t)ld_const(I.active, gk);
         l.rdy[x] = end;
         const uint32_t pqb = I.pq[(gk * I.g + s) * I.omp + mb];
-        start_out[j * I.g + s] = end + rs - (int)(pqb & 0xFFFFu);
+        start_out[j * I.g + s] = end + rs - word_p(pqb);
         mach_out[j * I.g + s] = mb;
       }
       __asm__ volatile("" ::: "memory");
@@ -737,14 +782,379 @@ __device__ __forceinline__ int decode_core(const DInst &I, const Lds &l, Prof &&
   return decode_core_rules<MAXM, PLAN, true>(I, l, prof, obj_out, work_out, start_out, mach_out,
                                              span_max);
 }
-// The narrow layout serves the default rules only (its callers check I.rules).
-template <int MAXM, bool PLAN, class Prof>
-__device__ __forceinline__ int decode_core(const DInst &I, const LdsN &l, Prof &&prof,
+
+// Earliest t >= t0 with every slot of [t, t + p) at most thr (Algorithm 2) over the
+// chip form's profile, a row of 64 slots at a time (at: slot `lane` of row 0); kNoRoom,
+// past any slots, if no such window ends within the first top rows.
+//
+// Up to 64 slots long (scan_rows): a stage's first op on each machine, whose window
+// starts under the previous stage's peak, is pushed past most of that stage (about
+// 1000 slots on the paper-shaped instance, in some 30 steps from hit to hit), so 16
+// rows are tested at once: a ballot per row gives lane r the clean slots of row r
+// (and, from lane r + 1, of the next), and each lane finds the runs of p clean slots
+// that start in its row by doubling (x &= x >> 1, 2, 4, ...).
+constexpr int kNoRoom = 1 << 17;
+__device__ __forceinline__ int scan_rows(const lds_u8 *at, int top, int t0, int p, uint32_t thr) {
+  const int lane = __lane_id();
+  for (int r = t0 >> 6; r < top; r += 15) {
+    uint32_t w0 = 0, w1 = 0;
+#pragma unroll
+    for (int i = 0; i < 16; i += 4) {
+      u64 m[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) m[k] = ballot64(at[min(r + i + k, top) * kWave] <= thr);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        w0 = (uint32_t)ffs_writelane((int)(uint32_t)m[k], i + k, (int)w0);
+        w1 = (uint32_t)ffs_writelane((int)(uint32_t)(m[k] >> 32), i + k, (int)w1);
+      }
+    }
+    uint32_t w2 = dpp<0x101>(w0), w3 = dpp<0x101>(w1);  // the next row, from lane + 1
+    auto step = [&](int k) {
+      w0 &= __builtin_amdgcn_alignbit(w1, w0, k);
+      w1 &= __builtin_amdgcn_alignbit(w2, w1, k);
+      w2 &= __builtin_amdgcn_alignbit(w3, w2, k);
+      w3 &= w3 >> k;
+    };
+    int len = 1;
+    for (; 2 * len <= min(p, 32); len *= 2) step(len);
+    if (p == 64) {
+      w0 &= w1;
+      w1 &= w2;
+    } else if (p > len) {
+      step(p - len);
+    }
+    if (r == t0 >> 6 && lane == 0) {
+      const u64 from = ~0ull << (t0 & 63);
+      w0 &= (uint32_t)from;
+      w1 &= (uint32_t)(from >> 32);
+    }
+    const u64 found = ballot64((w0 | w1) != 0) & 0x7FFFu;  // row 15 only looked ahead to
+    if (found) {
+      const int f = __ffsll((long long)found) - 1;
+      const u64 a = (u64)(uint32_t)__builtin_amdgcn_readlane((int)w1, f) << 32 |
+                    (uint32_t)__builtin_amdgcn_readlane((int)w0, f);
+      return ((r + f) << 6) + __ffsll((long long)a) - 1;
+    }
+  }
+  return kNoRoom;
+}
+// More than 64 slots: the window covers the rest of any row it starts in, so a row with
+// a hit moves t past its last one.
+__device__ __forceinline__ int scan_long(const lds_u8 *at, int top, int t0, int p, uint32_t thr) {
+  int t = t0, r = t0 >> 6;
+  uint32_t v = at[min(r, top) * kWave];
+  u64 from = ~0ull << (t0 & 63);
+  for (; r < top; ++r) {
+    const u64 m = ballot64(v > thr) & from;
+    v = at[(r + 1) * kWave];  // the last row's successor holds 255s
+    from = ~0ull;
+    const int b = t + p - (r << 6);  // the window's slots in this row end here
+    if (b <= kWave && (m & (~0ull >> (kWave - b))) == 0) return t;
+    if (m) t = (r << 6) + kWave - (int)__clzll(m);
+  }
+  return kNoRoom;
+}
+
+// The push-right of an op of p <= 64 slots that would end at slot e, from its hits among
+// the 64 slots that end there (bit i: slot e - 1 - i) and the hits `next` of the 64
+// from e on (bit i: slot e + 63 - i): from hit to hit while the window ends within
+// those. move: how far the window moves right; ok: no hit is left in it. By hand: the
+// compiler turns the conditions into lane masks, at twice the instructions.
+struct Hop {
+  int move;
+  bool ok;
+};
+__device__ __forceinline__ Hop hop(u64 hits, u64 next, int p) {
+  int c, f;
+  u64 t, low;
+  __asm__("s_bfm_b64 %[low], %[p], 0\n\t"
+          "s_cmp_eq_u32 %[p], 64\n\t"
+          "s_cselect_b64 %[low], -1, %[low]\n\t"
+          "s_ff1_i32_b64 %[f], %[h]\n\t"
+          "s_sub_u32 %[c], %[p], %[f]\n"  // the window starts after the last hit
+          "1:\n\t"                       // and ends at slot e + c
+          "s_sub_u32 %[f], 64, %[c]\n\t"
+          "s_lshr_b64 %[t], %[m], %[f]\n\t"
+          "s_and_b64 %[t], %[t], %[low]\n\t"
+          "s_cbranch_scc0 2f\n\t"
+          "s_ff1_i32_b64 %[f], %[t]\n\t"
+          "s_sub_u32 %[c], %[c], %[f]\n\t"
+          "s_add_u32 %[c], %[c], %[p]\n\t"
+          "s_cmp_le_u32 %[c], 64\n\t"
+          "s_cbranch_scc1 1b\n"
+          "2:"
+          : [c] "=&s"(c), [f] "=&s"(f), [t] "=&s"(t), [low] "=&s"(low)
+          : [h] "s"(hits), [m] "s"(next), [p] "s"(p)
+          : "scc");
+  return {c, c <= kWave};
+}
+
+// Decode the chromosome in l.gene under the default rules with the on-chip profile of the
+// chip form above. On kDecOk lane 0 has written *obj_out. Every lane calls this; the
+// result is uniform.
+//
+// Two things bound it. An op's chain: each placement reads the profile the one before
+// wrote; a dependent vector instruction costs 5 cycles on it, a value that crosses
+// from the vector to the scalar unit 20, an LDS read 50. And, with four waves on a
+// SIMD, the instructions: it issues one every 2 cycles, vector and scalar alike, one
+// of 8 bytes every 3. So each group of MAXM lanes holds the stage's machines, and a
+// DPP minimum over the keys gives every lane the winner's, e << 13 | machine << 9 |
+// long << 8 | Q with e the completion ignoring power: no scalar is needed to read the
+// 64 slots that end at e, one a lane from the last on, and P arrives while that read
+// is in flight. If none of the last P slots (lanes 0 to P - 1) breaks the peak the op
+// ends at e, and every lane writes its slot back (Q added within the window) behind
+// the next op's keys. A hit (10-40 % of the ops) moves the same lanes' window right
+// (hop, then scan_rows); an op longer than 64 slots always hits, by its key.
+//
+// Measured against the decoder that chose the machine on the scalar unit and read the
+// slots from the window's first on (an extra crossing and an alignment per read): a
+// decode of 4096 chromosomes 118 -> 80 us paper-shaped (50 jobs, 5 stages, 3 machines),
+// 950 -> 608 us at 200 jobs, 10 stages, 4-6 machines; of one 72 -> 49 and 610 -> 382 us;
+// instructions per op, paper-shaped, 96 -> 56. Two chromosomes in turn on one wave,
+// half as many waves a SIMD, were slower from 4096 chromosomes up (110 us).
+template <int MAXM, bool PLAN>
+__device__ int decode_chip(const DInst &I, const LdsN &l, int cap, int64_t *obj_out,
+                           int64_t *work_out, int32_t *start_out, int32_t *mach_out,
+                           int32_t *span_max) {
+  const int lane = __lane_id();
+  const int n = I.n, rs = I.rs, g = I.g;
+  const u64 below = (1ull << lane) - 1;
+  for (int x = lane; x < n; x += kWave) l.jobs[x] = 0xFFFF;
+  int bad = 0;
+  __asm__ volatile("" ::: "memory");
+  for (int k = lane; k < n; k += kWave) {
+    const int v = l.gene[k], j = ld_const(I.active, k);
+    l.rdy[k] = (uint16_t)min(max(ld_const(I.ready, j) - rs, 0), 0xFFFF);
+    if (v >= 1 && v <= n) l.jobs[n - v] = (uint16_t)(k | min(ld_const(I.first, j), 15) << 12);
+    else bad = 1;
+  }
+  __asm__ volatile("" ::: "memory");
+  // a rank no gene took: 0xFFFF, which no record is (gene 4095 only with first stage 15
+  // or later: that rank's gene is looked up)
+  for (int x = lane; x < n; x += kWave) {
+    const int jk = l.jobs[x];
+    bad |= jk == 0xFFFF && (n < kMaxGenes || l.gene[kMaxGenes - 1] != n - x);
+  }
+  if (ballot64(bad)) return kDecInval;
+
+  // Profile: the zeros before it and its own, the 255s after it, then the power held by
+  // the ops running at RS and by the planned ops kept in place.
+  const int top = cap >> 6;
+  lds_u8 *slot = (lds_u8 *)l.prof + kWave + lane;  // slot `lane` of row 0
+  for (int x = lane; x < cap / 4 + 16; x += kWave) ((uint32_t *)l.prof)[x] = 0;
+  if (lane < 32) ((uint32_t *)l.prof)[cap / 4 + 16 + lane] = ~0u;
+  __asm__ volatile("" ::: "memory");
+  for (int r = 0; r < I.nr; ++r) {
+    const int len = ld_const(I.running, 2 * r) - rs;
+    const int q = ld_const(I.running, 2 * r + 1);
+    if (len > cap) return kDecOverflow;
+    for (int x = 0; x < len - lane; x += kWave) slot[x] += (uint8_t)q;
+  }
+  for (int r = 0; r < I.nf; ++r) {
+    const int a = max(ld_const(I.fixed, 3 * r) - rs, 0), b = ld_const(I.fixed, 3 * r + 1) - rs;
+    const int q = ld_const(I.fixed, 3 * r + 2);
+    if (b > cap) return kDecOverflow;
+    for (int x = a; x < b - lane; x += kWave) slot[x] += (uint8_t)q;
+  }
+  __asm__ volatile("" ::: "memory");
+
+  // Ops go in chunks of C: their rows lie in l.rec, machine m's word of op k at word
+  // k * MAXM + m, loaded kWave words to a register one chunk ahead (the next stage's
+  // first chunk too, while its list of ops is this stage's).
+  constexpr int C = kChipChunk, NR = C * MAXM / kWave;
+  const int lk = lane / MAXM, lm = lane % MAXM;
+  const uint32_t qmax = (uint32_t)I.q_max;
+  // lane 0's slot of a window that ends at e is slot e - 1; a lane is in a window of P
+  // slots when below P (the compare reads P above its word's low bits: ones below)
+  lds_u8 *ends_at = (lds_u8 *)l.prof + kWave - 1 - lane;
+  const uint32_t dlow = (1u << kKeyBits) - 1, lane_p = (uint32_t)lane << kKeyBits | dlow;
+  __asm__("" : "+v"(ends_at));  // one register, no constant part to add at every use
+  uint32_t row[NR];
+  auto load_rows = [&](int s, int base, int cnt) {
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+      const int k = base + i * (kWave / MAXM) + lk;
+      const uint32_t off = ((uint32_t)l.op[min(k, cnt - 1)] * (uint32_t)g + (uint32_t)s) * MAXM + lm;
+      row[i] = *(const uint32_t *)((const uint8_t *)I.pq + (size_t)(off * 4u));
+    }
+  };
+  auto free_of = [&](int s) { return ld_const(I.mfree, (size_t)s * I.om + min(lm, I.om - 1)); };
+  int64_t work = 0;
+  uint64_t psum_all = 0;
+  lds_u8 *at = ends_at;  // the last op's slots, written behind the next op's keys
+  uint32_t vn = 0;
+  int cnt = 0, next_live = 0, over = 0;
+  int os_next = ld_const(I.nm, 0), free_next = free_of(0);
+  bool have = false;  // row holds the stage's first chunk
+  for (int s = 0; s < g && !over; ++s) {
+    const int os = os_next;
+    // this lane's machine's free time, like every time below << kKeyBits
+    // (a lane without a machine loses)
+    uint32_t fr = (uint32_t)(lm < os ? min(max(free_next - rs, 0), 0xFFFF) : kChipNoMachine)
+                  << kKeyBits;
+    if (s + 1 < g) {
+      os_next = ld_const(I.nm, s + 1);
+      free_next = free_of(s + 1);
+    }
+    // The stage's ops in decode order, as genes. The jobs of a stage are those of the
+    // one before and the jobs whose first unfrozen stage it is: the list stands until
+    // the least first stage still to come.
+    if (s >= next_live) {
+      const bool exact = g > 16 && s >= 15;
+      cnt = 0;
+      int nl = exact ? s + 1 : INT_MAX;
+      for (int b = 0; b < n; b += kWave) {
+        const int x = b + lane;
+        const uint32_t jk = x < n ? l.jobs[x] : 0u;
+        const bool live = x < n && live_at(I, jk, s, exact);
+        const u64 mk = ballot64(live);
+        if (live) l.op[cnt + __popcll(mk & below)] = (uint16_t)(jk & 0xFFF);
+        else if (x < n) nl = min(nl, max((int)(jk >> 12), s + 1));
+        cnt += __popcll(mk);
+      }
+#pragma unroll
+      for (int d = 32; d >= 1; d >>= 1) nl = min(nl, __shfl_xor(nl, d, kWave));
+      next_live = uni(nl);
+      cnt = uni(cnt);
+      __asm__ volatile("" ::: "memory");
+      have = false;
+    }
+    if (cnt == 0) continue;
+    if (!have) load_rows(s, 0, cnt);
+    int gene = l.op[min(lane & (C - 1), cnt - 1)];  // lane k < C: op k of the chunk
+    int ready = l.rdy[gene];
+    int64_t delay = 0;
+    uint32_t psum = 0;
+    const int all = cnt;
+    for (int base = 0; base < cnt; base += C) {
+#pragma unroll
+      for (int i = 0; i < NR; ++i) l.rec[i * kWave + lane] = row[i];
+      __asm__ volatile("" ::: "memory");
+      const uint32_t *recp = l.rec + lm;
+      uint32_t w = *recp;
+      int cn = uni(min(C, cnt - base));
+      const int nb = base + C;
+      // the next chunk, in flight during this one
+      have = nb < cnt || (s + 1 < g && s + 1 < next_live);
+      if (have) load_rows(nb < cnt ? s : s + 1, nb < cnt ? nb : 0, cnt);
+      const int gene_n = l.op[min(nb + (lane & (C - 1)), cnt - 1)];
+      const int ready_n = l.rdy[gene_n];
+      const int ext = ready << kKeyBits;
+      int ends = 0;  // lane k: the final key of the chunk's op k
+      for (int k = 0; k < cn; ++k) {
+        recp += MAXM;
+        const uint32_t w_next = *recp;  // one past the chunk's last row: read, not used
+        const uint32_t key = max((uint32_t)__builtin_amdgcn_readlane(ext, k), fr) + w;
+        *at = (uint8_t)vn;  // the previous op's slots
+        const uint32_t kmin = group_min<MAXM>(key);
+        at = ends_at + min(kmin >> kKeyBits, (uint32_t)(cap + kWave));
+        const uint32_t v = *at;
+        const bool win = key == kmin;
+        int sk = uni((int)kmin);
+        const uint32_t sw = (uint32_t)__builtin_amdgcn_readlane((int)w, (sk >> 9) & 15);
+        const uint32_t qin = lane_p < sw ? kmin & 0x1FFu : 0u;
+        fr = win ? kmin & ~dlow : fr;
+        ends = ffs_writelane(sk, k, ends);
+        __builtin_amdgcn_sched_barrier(0);  // all of that while the read is in flight
+        vn = v + qin;
+        u64 hits = ballot64(vn > qmax);
+        if (__builtin_expect(hits != 0, 0)) {
+          const int e0 = (int)((uint32_t)sk >> kKeyBits), sp = word_p(sw), sq = sk & 0xFF;
+          const uint32_t thr = qmax - (uint32_t)sq;
+          int e;
+          if (__builtin_expect(sk & (int)kLongOp, 0)) {
+            // the 64 slots before those at hand, and the window's share of them
+            const uint32_t v1 = at[-kWave];
+            const bool in1 = lane + kWave < sp;
+            e = sp <= 2 * kWave ? e0 : kNoRoom;
+            if (ballot64(max(v, in1 ? v1 : 0u) > thr)) e = kNoRoom;
+            if (e <= cap) {
+              at[-kWave] = (uint8_t)(v1 + (in1 ? (uint32_t)sq : 0u));
+              vn = v + (uint32_t)sq;
+            } else {
+              e = scan_long(slot, top, e0 - sp, sp, thr) + sp;
+              at = ends_at;  // the zeros before the profile, written again
+              vn = 0;
+              if (e <= cap)
+                for (int x = e - sp; x < e - lane; x += kWave) slot[x] += (uint8_t)sq;
+            }
+          } else {
+            const uint32_t v1 = at[kWave];
+            hits &= ballot64(qin != 0);  // (not a slot outside that was over the peak before)
+            e = e0;
+            if (hits) {
+              const Hop h = hop(hits, ballot64(v1 > thr), sp);
+              e += h.move;
+              if (__builtin_expect(!h.ok, 0)) e = scan_rows(slot, top, e - sp, sp, thr) + sp;
+              at = ends_at + min(e, cap + kWave);
+              vn = *at + qin;
+            }
+          }
+          if (__builtin_expect(e > cap, 0)) {  // outgrows the slots: the rest is left
+            over = 1;
+            cn = cnt = 0;
+          }
+          sk += (e - e0) << kKeyBits;
+          fr = win ? (uint32_t)sk & ~dlow : fr;
+          ends = ffs_writelane(sk, k, ends);
+          delay += e - e0;
+        }
+        w = w_next;
+      }
+      // the chunk's ends, and with a plan the ops' starts and machines
+      if (lane < cn) {
+        const int end = (int)((uint32_t)ends >> kKeyBits), mb = (ends >> 9) & 15;
+        const int p = word_p(l.rec[lane * MAXM + mb]);
+        psum += p;
+        l.rdy[gene] = (uint16_t)end;
+        if (PLAN) {
+          const size_t j = (size_t)ld_const(I.active, gene);
+          start_out[j * g + s] = end + rs - p;
+          mach_out[j * g + s] = mb;
+        }
+      }
+      __asm__ volatile("" ::: "memory");
+      gene = gene_n;
+      ready = ready_n;
+    }
+    psum_all += psum;
+    work += delay + (int64_t)3 * os * all;
+  }
+  if (over) return kDecOverflow;
+  work += 2 * wave_sum64((int64_t)psum_all);
+  // Objective, eqs. (1)-(3), over every job in J u J'.
+  int64_t tard = 0;
+  int cmax = 0;
+  for (int k = lane; k < n; k += kWave) {
+    const int c = (int)l.rdy[k] + rs;
+    const int late = c - ld_const(I.due_k, k);
+    tard += late > 0 ? late : 0;
+    cmax = max(cmax, c);
+  }
+  tard = wave_sum64(tard);
+  cmax = wave_max32(cmax);
+  if (span_max && lane == 0) atomicMax(span_max, cmax - rs);  // profile slots this decode used
+  cmax = max(cmax, I.frozen_cmax);
+  if (lane == 0) {
+    *obj_out = (int64_t)I.wt * (I.frozen_t + tard) + cmax;
+    if (work_out) *work_out = work;
+  }
+  return kDecOk;
+}
+template <int MAXM, bool PLAN>
+__device__ __forceinline__ int decode_core(const DInst &I, const LdsN &l, const LdsProfile &prof,
                                            int64_t *obj_out, int64_t *work_out,
                                            int32_t *start_out, int32_t *mach_out,
                                            int32_t *span_max = nullptr) {
-  return decode_core_rules<MAXM, false, false>(I, l, prof, obj_out, work_out, start_out, mach_out,
-                                               span_max);
+  return decode_chip<MAXM, PLAN>(I, l, prof.cap, obj_out, work_out, start_out, mach_out, span_max);
+}
+
+// `body` on the LDS layout that a decode with `cap` on-chip slots takes.
+template <class F>
+__device__ __forceinline__ auto in_layout(const DInst &I, int cap, uint8_t *smem, F body) {
+  if (chip_rules(I.rules, cap)) return body(carve_lds_n(smem, I.n, I.omp));
+  return body(carve_lds(smem, I.n));
 }
 
 __device__ void flag_error(Header *h, int status) {
@@ -771,15 +1181,16 @@ __global__ __launch_bounds__(64) void decode_kernel(DInst I, const int32_t *__re
                                                     int cap) {
   extern __shared__ __align__(16) uint8_t smem[];
   const int i = blockIdx.x;
-  Lds l = carve_lds(smem, I.n);
   const int32_t *src = prio + (size_t)i * I.n;
-  for (int k = __lane_id(); k < I.n; k += kWave) l.gene[k] = src[k];
-  __asm__ volatile("" ::: "memory");
   const size_t plan = (size_t)i * I.n_jobs * I.g;
-  const LdsProfile prof{l.prof, cap};
   int64_t *w = work ? work + i : nullptr;
-  const int st = start ? decode_core<MAXM, true>(I, l, prof, obj + i, w, start + plan, mach + plan)
-                       : decode_core<MAXM, false>(I, l, prof, obj + i, w, nullptr, nullptr);
+  const int st = in_layout(I, cap, smem, [&](const auto &l) {
+    for (int k = __lane_id(); k < I.n; k += kWave) l.gene[k] = src[k];
+    __asm__ volatile("" ::: "memory");
+    const LdsProfile prof{l.prof, cap};
+    return start ? decode_core<MAXM, true>(I, l, prof, obj + i, w, start + plan, mach + plan)
+                 : decode_core<MAXM, false>(I, l, prof, obj + i, w, nullptr, nullptr);
+  });
   if (st == kDecOk) return;
   if (__lane_id() == 0) obj[i] = -1;
   if (st == kDecOverflow) push_overflow(hdr, ovf_list, i);
@@ -846,9 +1257,8 @@ struct GaDev {
   size_t redo_stride;
   u64 seed, shop;
   // islands: the islands a generation launch covers, from island isl0 on (the
-  // whole population but for ga_step's island groups); narrow: the generation
-  // and init kernels take the narrow LDS layout (LdsN)
-  int32_t event, rows, cols, islands, mig_k, isl0, narrow;
+  // whole population but for ga_step's island groups)
+  int32_t event, rows, cols, islands, mig_k, isl0;
   uint32_t pc, pm;
 };
 
@@ -1207,15 +1617,14 @@ __global__ __launch_bounds__(64) void classical_generation_kernel(DInst I, GaDev
                                                                   int cap, const u64 *prefix) {
   extern __shared__ __align__(16) uint8_t smem[];
   const int i = blockIdx.x, pop = A.rows * A.cols, partner = i ^ 1;
-  const Lds l = carve_lds(smem, I.n);
   const int32_t *mine = A.prio_in + (size_t)roulette_spin(A, prefix, pop, i, gen) * I.n;
-  if (partner < pop) {
-    const int32_t *other = A.prio_in + (size_t)roulette_spin(A, prefix, pop, partner, gen) * I.n;
-    build_child(A, I.n, i, gen, l, mine, other, i & ~1, 0, true);
-  } else {
-    build_child(A, I.n, i, gen, l, mine, mine, -1, 0, true);
-  }
-  decode_and_record<MAXM>(I, A, i, cap, l, i);
+  const int32_t *other = mine;
+  if (partner < pop)
+    other = A.prio_in + (size_t)roulette_spin(A, prefix, pop, partner, gen) * I.n;
+  in_layout(I, cap, smem, [&](const auto &l) {
+    build_child(A, I.n, i, gen, l, mine, other, partner < pop ? i & ~1 : -1, 0, true);
+    decode_and_record<MAXM>(I, A, i, cap, l, i);
+  });
 }
 
 // Cellular GA, one wave per cell: the best two of the cell and its four torus
@@ -1226,7 +1635,6 @@ __global__ __launch_bounds__(64) void cellular_generation_kernel(DInst I, GaDev 
                                                                  int cap) {
   extern __shared__ __align__(16) uint8_t smem[];
   const int i = blockIdx.x, R = A.rows, C = A.cols, r = i / C, c = i % C;
-  const Lds l = carve_lds(smem, I.n);
   const int cand[5] = {i, ((r + R - 1) % R) * C + c, ((r + 1) % R) * C + c,
                        r * C + (c + C - 1) % C, r * C + (c + 1) % C};
   int64_t o[5];
@@ -1239,9 +1647,11 @@ __global__ __launch_bounds__(64) void cellular_generation_kernel(DInst I, GaDev 
 #pragma unroll
   for (int k = 0; k < 5; ++k)
     if (k != b1 && (b2 < 0 || o[k] < o[b2])) b2 = k;
-  build_child(A, I.n, i, gen, l, A.prio_in + (size_t)cand[b1] * I.n,
-              A.prio_in + (size_t)cand[b2] * I.n, i, 0, true);
-  decode_and_record<MAXM>(I, A, i, cap, l, i);
+  in_layout(I, cap, smem, [&](const auto &l) {
+    build_child(A, I.n, i, gen, l, A.prio_in + (size_t)cand[b1] * I.n,
+                A.prio_in + (size_t)cand[b2] * I.n, i, 0, true);
+    decode_and_record<MAXM>(I, A, i, cap, l, i);
+  });
 }
 
 // Cellular replacement: a cell keeps its previous individual unless the child
@@ -1281,15 +1691,10 @@ __global__ __launch_bounds__(64) void ga_generation_kernel(DInst I, GaDev A, int
   extern __shared__ __align__(16) uint8_t smem[];
   const int K = A.rows * A.cols;
   const int i = A.isl0 * K + slot_of_block(blockIdx.x, K, A.islands);
-  if (A.narrow) {  // the narrow layout (lds_bytes_n): default rules only
-    const LdsN l = carve_lds_n(smem, I.n);
+  in_layout(I, cap, smem, [&](const auto &l) {
     breed_child(A, I.n, i, gen, l);
     decode_and_record<MAXM>(I, A, i, cap, l, i);
-  } else {
-    const Lds l = carve_lds(smem, I.n);
-    breed_child(A, I.n, i, gen, l);
-    decode_and_record<MAXM>(I, A, i, cap, l, i);
-  }
+  });
 }
 
 // Generation 0. span: null, or where the longest schedule is recorded
@@ -1298,20 +1703,19 @@ template <int MAXM>
 __global__ __launch_bounds__(64) void ga_init_kernel(DInst I, GaDev A, int cap, int32_t *span) {
   extern __shared__ __align__(16) uint8_t smem[];
   const int i = blockIdx.x;
-  if (A.narrow) {  // the narrow layout (lds_bytes_n): default rules only
-    const LdsN l = carve_lds_n(smem, I.n);
+  in_layout(I, cap, smem, [&](const auto &l) {
     init_child(A, I.n, i, l);
     decode_and_record<MAXM>(I, A, i, cap, l, i, span);
-  } else {
-    const Lds l = carve_lds(smem, I.n);
-    init_child(A, I.n, i, l);
-    decode_and_record<MAXM>(I, A, i, cap, l, i, span);
-  }
+  });
 }
 
-// LDS of the generation and init kernels in the layout they take.
-size_t lds_bytes_gen(const ffs_instance *in, int cap, bool narrow) {
-  return narrow ? lds_bytes_n(in->n_active, cap) : lds_bytes(in->n_active, cap);
+// Row width of the packed table.
+int omp_of(int om) { return om <= 4 ? 4 : om <= 8 ? 8 : 16; }
+
+// LDS of a decode with `cap` on-chip slots in the layout it takes.
+size_t lds_bytes_of(const ffs_instance *in, int cap) {
+  return chip_rules(in->decode_rules, cap) ? lds_bytes_n(in->n_active, omp_of(in->o_max), cap)
+                                           : lds_bytes(in->n_active, cap);
 }
 
 // ---------------------------------------------------------------------------
@@ -1512,7 +1916,7 @@ __device__ int decode_xy_core_t(const DInst &I, const XyTab &T, const LdsXy &l, 
       const int r1 = NB > 1 ? __builtin_amdgcn_readlane(rv1, xl) : 0;
       const bool hi = NB > 1 && x >= kWave;
       const int est = max(rs, hi ? r1 : r0), fr = __builtin_amdgcn_readlane(fmv, f);
-      const int p = pqw & 0xFFFF, q = (int)((uint32_t)pqw >> 16);
+      const int p = word_p((uint32_t)pqw), q = word_q((uint32_t)pqw);
       const int t0 = max(est, fr) - rs;
       prof.commit(ct, cp, cq);
       const int t = prof.place(t0, p, (uint32_t)(I.q_max - q));
@@ -1547,7 +1951,7 @@ __device__ int decode_xy_core_t(const DInst &I, const XyTab &T, const LdsXy &l, 
       const int xfn = uni(rec.x), xn = xfn & 0xFFF, fn = xfn >> 12;
       rdy_n = l.rdy[xn];
       fm_n = l.fm[fn];
-      const int p = pqw & 0xFFFF, q = (int)((uint32_t)pqw >> 16);
+      const int p = word_p((uint32_t)pqw), q = word_q((uint32_t)pqw);
       const uint32_t thr = (uint32_t)(I.q_max - q);
       const int t0 = max(est, fr) - rs;
       const int t = prof.place(t0, p, thr);
@@ -1893,23 +2297,24 @@ __global__ __launch_bounds__(64) void ga_screened_kernel(DInst I, GaDev A, int g
   extern __shared__ __align__(16) uint8_t smem[];
   const int K = A.rows * A.cols;
   const int i = A.isl0 * K + slot_of_block(blockIdx.x, K, A.islands);
-  const Lds l = carve_lds(smem, I.n);
-  const float b3 = theta[FFS_SG_PARAMS - 1];
-  int best = 0;
-  float best_s = 0.f;
-  for (int v = 0; v < V; ++v) {
-    breed_child(A, I.n, i, gen, l, v, false);
-    const float sv = score_genes(l.gene, I.n, table, b3);
-    if (scores && __lane_id() == 0) scores[(size_t)v * pop + i] = sv;
-    if (v == 0 || sv < best_s) {
-      best_s = sv;
-      best = v;
+  in_layout(I, cap, smem, [&](const auto &l) {
+    const float b3 = theta[FFS_SG_PARAMS - 1];
+    int best = 0;
+    float best_s = 0.f;
+    for (int v = 0; v < V; ++v) {
+      breed_child(A, I.n, i, gen, l, v, false);
+      const float sv = score_genes(l.gene, I.n, table, b3);
+      if (scores && __lane_id() == 0) scores[(size_t)v * pop + i] = sv;
+      if (v == 0 || sv < best_s) {
+        best_s = sv;
+        best = v;
+      }
+      __asm__ volatile("" ::: "memory");
     }
-    __asm__ volatile("" ::: "memory");
-  }
-  if (choice && __lane_id() == 0) choice[i] = best;
-  breed_child(A, I.n, i, gen, l, best, true);
-  decode_and_record<MAXM>(I, A, i, cap, l, i);
+    if (choice && __lane_id() == 0) choice[i] = best;
+    breed_child(A, I.n, i, gen, l, best, true);
+    decode_and_record<MAXM>(I, A, i, cap, l, i);
+  });
 }
 
 // Block-wide (value, index) reductions with the lowest index on ties.
@@ -2150,7 +2555,6 @@ __device__ __forceinline__ GaDev slot_ga(const BatchSlot &S, const BatchArgs &B,
   A.cols = B.cols;
   A.islands = B.islands;
   A.isl0 = 0;
-  A.narrow = 0;
   A.mig_k = B.mig_k;
   A.pc = B.pc;
   A.pm = B.pm;
@@ -2160,18 +2564,19 @@ __device__ __forceinline__ GaDev slot_ga(const BatchSlot &S, const BatchArgs &B,
 // Decode the child in l.gene (already stored in A.prio_out) with the on-chip
 // profile; a decode that outgrows it is redone at once with this block's
 // off-chip profile.
-template <int MAXM>
-__device__ void decode_slot(const DInst &I, const GaDev &A, int i, int cap, const Lds &l,
+template <int MAXM, class L>
+__device__ void decode_slot(const DInst &I, const GaDev &A, int i, int cap, const L &l,
                             const GlobalProfile &gp, int32_t *span_max = nullptr) {
   int64_t work = 0;
   int st = decode_core<MAXM, false>(I, l, LdsProfile{l.prof, cap}, A.obj_out + i, &work, nullptr,
                                     nullptr, span_max);
   if (st == kDecOverflow) {
+    const Lds lw = carve_lds((uint8_t *)l.rdy, I.n);  // both layouts start at rdy
     const int32_t *src = A.prio_out + (size_t)i * I.n;
-    for (int k = __lane_id(); k < I.n; k += kWave) l.gene[k] = src[k];
+    for (int k = __lane_id(); k < I.n; k += kWave) lw.gene[k] = src[k];
     __asm__ volatile("" ::: "memory");
     work = 0;
-    st = decode_core<MAXM, false>(I, l, gp, A.obj_out + i, &work, nullptr, nullptr, span_max);
+    st = decode_core<MAXM, false>(I, lw, gp, A.obj_out + i, &work, nullptr, nullptr, span_max);
   }
   if (st == kDecOk) {
     if (__lane_id() == 0) atomicAdd(&A.hdr->work, (unsigned long long)work);
@@ -2197,20 +2602,15 @@ __global__ __launch_bounds__(64) void batch_generation_kernel(BatchArgs B, int c
     if (!S.active || S.cls != cls) continue;
     const int gen = S.gen + 1;
     const GaDev A = slot_ga(S, B, gen);
-    const Lds l = carve_lds(smem, S.I.n);
     const GlobalProfile gp{gp_mem, offchip_cap(S.I.horizon)};
-    if (ISLAND) {
-      const int isl = item % per_slot;
-      for (int k = 0; k < K; ++k) {
-        breed_child(A, S.I.n, isl * K + k, gen, l);
-        decode_slot<MAXM>(S.I, A, isl * K + k, S.cap, l, gp);
+    const int first = ISLAND ? item % per_slot * K : item % per_slot;
+    in_layout(S.I, S.cap, smem, [&](const auto &l) {
+      for (int i = first; i < first + (ISLAND ? K : 1); ++i) {
+        breed_child(A, S.I.n, i, gen, l);
+        decode_slot<MAXM>(S.I, A, i, S.cap, l, gp);
       }
-      replace_island_wave(A, isl, K, S.I.n);
-    } else {
-      const int i = item % per_slot;
-      breed_child(A, S.I.n, i, gen, l);
-      decode_slot<MAXM>(S.I, A, i, S.cap, l, gp);
-    }
+    });
+    if (ISLAND) replace_island_wave(A, item % per_slot, K, S.I.n);
   }
 }
 
@@ -2223,12 +2623,13 @@ __global__ __launch_bounds__(64) void batch_init_kernel(BatchArgs B, int d) {
   GaDev A0 = A;
   A0.prio_out = S.prio[0];
   A0.obj_out = S.obj[0];
-  const Lds l = carve_lds(smem, S.I.n);
   const GlobalProfile gp{B.gprof + B.gstride * blockIdx.x, offchip_cap(S.I.horizon)};
-  for (int i = blockIdx.x; i < B.pop; i += gridDim.x) {
-    init_child(A0, S.I.n, i, l);
-    decode_slot<MAXM>(S.I, A0, i, S.cap, l, gp, &B.slots[d].span);
-  }
+  in_layout(S.I, S.cap, smem, [&](const auto &l) {
+    for (int i = blockIdx.x; i < B.pop; i += gridDim.x) {
+      init_child(A0, S.I.n, i, l);
+      decode_slot<MAXM>(S.I, A0, i, S.cap, l, gp, &B.slots[d].span);
+    }
+  });
 }
 
 // Profile size class of slot d from its generation 0: the smallest of
@@ -2303,7 +2704,7 @@ __global__ __launch_bounds__(64) void clear_header_kernel(Header *h) {
 }
 
 // The decoders' per-instance table: row k * g + s holds stage s of active job
-// k (gene order) as P | Q << 16 per machine, omp words (zero past o_max); the
+// k (gene order) as one pack_word per machine, omp words (zero past o_max); the
 // n words after the rows hold the active jobs' due dates.
 __global__ void pack_kernel(const int32_t *proc, const int32_t *power, const int32_t *due,
                             const int32_t *active, uint32_t *pq, int n, int g, int om, int omp) {
@@ -2316,7 +2717,7 @@ __global__ void pack_kernel(const int32_t *proc, const int32_t *power, const int
     uint32_t v = 0;
     if (m < om) {
       const size_t src = ((size_t)active[k] * g + st) * om + m;
-      v = ((uint32_t)proc[src] & 0xFFFFu) | (((uint32_t)power[src] & 0xFFFFu) << 16);
+      v = pack_word((uint32_t)proc[src], (uint32_t)power[src], (uint32_t)m);
     }
     pq[x] = v;
   }
@@ -2677,7 +3078,6 @@ int max_lds_bytes() {
   return v;
 }
 
-int omp_of(int om) { return om <= 4 ? 4 : om <= 8 ? 8 : 16; }
 
 int check_host(const ffs_instance *in) {
   if (!in) return FFS_E_INVAL;
@@ -2778,7 +3178,7 @@ int run_decode(const ffs_instance *in, const int32_t *prio, int32_t pop, int64_t
                int32_t *start, int32_t *mach, int64_t *work, int cap, const DecodeLayout &L,
                hipStream_t stream) {
   const DInst d = make_dinst(in, L.pq);
-  const size_t shmem = lds_bytes(in->n_active, cap);
+  const size_t shmem = lds_bytes_of(in, cap);
   hipError_t e = launch(0, decode_kernel<MAXM>, dim3(pop), dim3(kWave), shmem, stream, d, prio, obj,
                         work, start, mach, L.hdr, L.ovf_list, cap);
   if (e != hipSuccess) return FFS_E_DEVICE;
@@ -2969,7 +3369,6 @@ GaDev make_gadev(const ffs_ga *ga, const GaLayout &L, int in_buf) {
   A.cols = ga->params.cols;
   A.islands = ga->params.islands;
   A.isl0 = 0;
-  A.narrow = 0;
   A.mig_k = ga->params.mig_k;
   A.pc = ga->params.pc;
   A.pm = ga->params.pm;
@@ -3015,26 +3414,6 @@ int waves_per_cu(size_t bytes) {
   return b;
 }
 
-int n_cus() {
-  int dev = 0, v = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-    return 0;
-  return v;
-}
-
-// Whether the generation and init kernels take the narrow layout: under the
-// default rules, and only where it lets a compute unit hold more waves of a
-// population that the chip cannot hold at once in the wide layout (otherwise
-// the narrow form's extra masking buys nothing).
-template <int MAXM>
-bool use_narrow(const ffs_instance *in, int cap, int pop) {
-  if (in->decode_rules != 0) return false;
-  const int ww = waves_per_cu<MAXM>(lds_bytes(in->n_active, cap));
-  const int wn = waves_per_cu<MAXM>(lds_bytes_n(in->n_active, cap));
-  return wn > ww && (int64_t)pop > (int64_t)ww * n_cus();
-}
-
 template <int MAXM>
 int ga_init_impl(ffs_ga *ga, const ffs_instance *in, const GaLayout &L, hipStream_t stream,
                  bool auto_cap) {
@@ -3042,7 +3421,7 @@ int ga_init_impl(ffs_ga *ga, const ffs_instance *in, const GaLayout &L, hipStrea
   GaDev A = make_gadev(ga, L, 1);  // generation 0 is written to buffer 0
   const int pop = ga->pop, cap = ga->lds_slots, n = ga->n_genes;
   const int K = ga->params.rows * ga->params.cols;
-  const bool xy = ga->params.encoding == 1, hybrid = ga->params.scheme == FFS_GA_HYBRID;
+  const bool xy = ga->params.encoding == 1;
   int rc;
   if (xy) {
     if ((rc = build_xy_table(in, L.xyop, L.xyg0, stream))) return rc;
@@ -3051,9 +3430,7 @@ int ga_init_impl(ffs_ga *ga, const ffs_instance *in, const GaLayout &L, hipStrea
                XyTab{L.xyop, L.xyg0, in->n_ops}, A, cap) != hipSuccess)
       return FFS_E_DEVICE;
   } else {
-    A.narrow = hybrid && use_narrow<MAXM>(in, cap, pop);
-    if (launch(1, ga_init_kernel<MAXM>, dim3(pop), dim3(kWave), lds_bytes_gen(in, cap, A.narrow),
-               stream, d, A, cap, auto_cap ? &L.hdr->span_max : (int32_t *)nullptr) != hipSuccess)
+    if (launch(1, ga_init_kernel<MAXM>, dim3(pop), dim3(kWave), lds_bytes_of(in, cap), stream, d, A, cap, auto_cap ? &L.hdr->span_max : (int32_t *)nullptr) != hipSuccess)
       return FFS_E_DEVICE;
   }
   rc = ga_overflow<MAXM>(in, L, 0, cap, stream, xy, auto_cap ? &L.hdr->span_max : nullptr);
@@ -3075,13 +3452,11 @@ int ga_init_impl(ffs_ga *ga, const ffs_instance *in, const GaLayout &L, hipStrea
     const int64_t span = host.span_max, top = probe_cap(in, kAutoSlots);
     int64_t lo = (int64_t)align_up((size_t)(span + span / 64 + 64), 64);
     if (lo > top) lo = top;
-    // the layout the generations will take at lo sets the bytes per slot count
-    const bool narrow = hybrid && use_narrow<MAXM>(in, (int)lo, pop);
-    const int w = waves_per_cu<MAXM>(lds_bytes_gen(in, (int)lo, narrow));
+    const int w = waves_per_cu<MAXM>(lds_bytes_of(in, (int)lo));
     int64_t a = lo / 64, b = top / 64;  // waves_per_cu falls as the slots grow
     while (w > 0 && a < b) {
       const int64_t m = (a + b + 1) / 2;
-      if (waves_per_cu<MAXM>(lds_bytes_gen(in, (int)(m * 64), narrow)) >= w)
+      if (waves_per_cu<MAXM>(lds_bytes_of(in, (int)(m * 64))) >= w)
         a = m;
       else
         b = m - 1;
@@ -3176,7 +3551,7 @@ bool migrate(const ffs_ga_params &p, const GaLayout &L, int cur, int n, hipStrea
 // holds islands [islands * g / G, islands * (g + 1) / G).
 template <int MAXM>
 int ga_step_groups(ffs_ga *ga, const ffs_instance *in, const GaLayout &L, int32_t n_gen,
-                   hipStream_t stream, int G, size_t shmem, const Screen *scr, bool narrow) {
+                   hipStream_t stream, int G, size_t shmem, const Screen *scr) {
   std::lock_guard<std::mutex> lk(g_group_mu);
   GroupStreams *GS = nullptr;
   int rc = group_streams(&GS);
@@ -3208,7 +3583,6 @@ int ga_step_groups(ffs_ga *ga, const ffs_instance *in, const GaLayout &L, int32_
       GaDev A = make_gadev(ga, L, cur);
       A.isl0 = i0;
       A.islands = i1 - i0;
-      A.narrow = narrow;
       const dim3 grid((unsigned)((i1 - i0) * K));
       const hipError_t e =
           scr ? launch(5, ga_screened_kernel<MAXM>, grid, dim3(kWave), shmem, sg, d, A, gen, cap,
@@ -3242,12 +3616,9 @@ int ga_step_impl(ffs_ga *ga, const ffs_instance *in, int32_t n_gen, hipStream_t 
   const int K = ga->params.rows * ga->params.cols;
   const bool xy = ga->params.encoding == 1;
   const XyTab T{L.xyop, L.xyg0, in->n_ops};
-  // shmem: the screened and comparison kernels; shmem_gen: the generation kernel
   const size_t shmem = xy ? lds_bytes_xy(in->n_active, in->n_ops, in->n_stages, in->o_max, cap)
-                          : lds_bytes(in->n_active, cap);
-  const bool narrow = !xy && ga->params.scheme == FFS_GA_HYBRID && use_narrow<MAXM>(in, cap, pop);
-  const size_t shmem_gen = xy ? shmem : lds_bytes_gen(in, cap, narrow);
-  ga->narrow_lds = narrow && !scr;
+                          : lds_bytes_of(in, cap);
+  ga->narrow_lds = !xy && chip_rules(in->decode_rules, cap);
   // Island groups for the hybrid GA whose overflowed decodes are redone by their
   // own waves (the overflow kernel's list belongs to the whole population).
   if (ga->params.scheme == FFS_GA_HYBRID && (cap >= in->horizon || L.inline_redo)) {
@@ -3256,8 +3627,7 @@ int ga_step_impl(ffs_ga *ga, const ffs_instance *in, int32_t n_gen, hipStream_t 
     if (G > ga->params.islands) G = ga->params.islands;
     if (G > 1) {
       ga->island_groups = G;
-      return ga_step_groups<MAXM>(ga, in, L, n_gen, stream, G, scr ? shmem : shmem_gen, scr,
-                                  narrow && !scr);
+      return ga_step_groups<MAXM>(ga, in, L, n_gen, stream, G, shmem, scr);
     }
   }
   ga->island_groups = 1;
@@ -3265,7 +3635,6 @@ int ga_step_impl(ffs_ga *ga, const ffs_instance *in, int32_t n_gen, hipStream_t 
     const int gen = ga->generation + 1;
     const int cur = ga->cur;
     GaDev A = make_gadev(ga, L, cur);
-    A.narrow = narrow;
     hipError_t e;
     const int32_t scheme = ga->params.scheme;
     if (scheme == FFS_GA_CLASSICAL) {
@@ -3284,7 +3653,7 @@ int ga_step_impl(ffs_ga *ga, const ffs_instance *in, int32_t n_gen, hipStream_t 
       e = launch(1, ga_generation_xy_kernel, dim3(pop), dim3(kWave), shmem, stream, d, T, A, gen,
                  cap);
     else
-      e = launch(1, ga_generation_kernel<MAXM>, dim3(pop), dim3(kWave), shmem_gen, stream, d, A,
+      e = launch(1, ga_generation_kernel<MAXM>, dim3(pop), dim3(kWave), shmem, stream, d, A,
                  gen, cap);
     if (e != hipSuccess) return FFS_E_DEVICE;
     int rc = ga_overflow<MAXM>(in, L, 1 - cur, cap, stream, xy);
@@ -3432,6 +3801,13 @@ int batch_cap(const ffs_batch_params *p) {
   return cap > h ? h : cap;
 }
 
+// LDS of a batch's decodes: room for the layouts of both kinds of decode rules.
+size_t batch_lds(const ffs_batch_params *p, int cap) {
+  const size_t wide = lds_bytes(p->max_genes, cap);
+  const size_t chip = cap <= kChipSlots ? lds_bytes_n(p->max_genes, omp_of(p->o_max), cap) : 0;
+  return wide > chip ? wide : chip;
+}
+
 BatchArgs batch_args(const ffs_batch *b, const BatchLayout &L) {
   BatchArgs B;
   B.slots = L.slots;
@@ -3459,7 +3835,7 @@ int batch_generation_launches(const ffs_batch *b, const BatchArgs &B, hipStream_
   hipError_t e = hipSuccess;
   // one launch per profile size class, each with that class's LDS
   for (int c = 0; c < n_cls && e == hipSuccess; ++c) {
-    const size_t shmem = lds_bytes(p.max_genes, b->lds_slots >> (n_cls - 1 - c));
+    const size_t shmem = batch_lds(&p, b->lds_slots >> (n_cls - 1 - c));
     if (p.schedule == FFS_SCHEDULE_ISLAND)
       e = launch(timed ? 4 : -1, batch_generation_kernel<MAXM, true>, dim3(b->blocks), dim3(kWave),
                  shmem, s, B, c);
@@ -3506,7 +3882,7 @@ int batch_init_launch(const ffs_batch *b, const BatchArgs &B, int slot, const Ba
                       hipStream_t s) {
   set_batch_lds_limits<MAXM>();
   const ffs_batch_params &p = b->params;
-  const size_t shmem = lds_bytes(p.max_genes, b->lds_slots);
+  const size_t shmem = batch_lds(&p, b->lds_slots);
   const int grid = b->pop < b->blocks ? b->pop : b->blocks;
   if (launch(-1, batch_init_kernel<MAXM>, dim3(grid), dim3(kWave), shmem, s, B, slot) != hipSuccess ||
       launch(-1, batch_class_kernel, dim3(1), dim3(kWave), 0, s, B, slot, batch_classes(&p),

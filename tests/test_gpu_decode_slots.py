@@ -1,0 +1,62 @@
+"""The default-rules decoder on its on-chip profile (ffs_decode through the C ABI) where its
+64-slot windows, its rows of 64 slots and its chunks of 16 ops end, against the CPU oracle.
+
+Integer path: objectives, start times, machines and work counts are identical (zero tolerance).
+"""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1903_10741_amd import workloads as W
+from test_gpu_decode import _compare, _say
+
+pytestmark = pytest.mark.gpu
+
+
+def _instance(n, machines, times, powers, q_max, seed, running=(), fixed=()):
+    """n jobs whose P and Q are drawn from `times` and `powers`."""
+    rng = np.random.default_rng(seed)
+    shape = (n, len(machines), max(machines))
+    inst = W.initial_instance(rng.choice(times, size=shape), rng.choice(powers, size=shape),
+                              np.zeros(n, np.int32), np.full(n, 50, np.int32), machines, q_max, 3)
+    inst.running = np.asarray(running, np.int32).reshape(-1, 2)
+    if len(fixed):
+        inst.fixed = np.asarray(fixed, np.int32).reshape(-1, 3)
+    return inst
+
+
+CASES = {
+    # windows of one row, one more, two rows and one more; 4, 8 and 16 lanes a stage
+    "p 63-65": (40, [3, 2], [1, 63, 64, 65], [1, 4, 6], 9, [], []),
+    "p 127-129": (30, [5, 8], [64, 127, 128, 129, 200], [2, 5], 9, [], []),
+    "sixteen machines": (35, [16, 9, 1], [1, 2, 31, 32, 33, 64], [1, 3], 12, [], []),
+    # every op draws the whole peak: pushed past all before it, further than the 15 rows
+    # searched at once
+    "whole peak": (120, [16], [50, 63, 64], [7], 7, [], []),
+    "whole peak, long": (60, [4], [65, 128, 129], [7], 7, [], []),
+    "byte peak": (33, [4, 4], [3, 40, 64, 65], [1, 100, 255], 255, [], []),
+    "unit ops": (129, [4, 4, 4], [1], [1], 2, [], []),
+    # ops that run at RS past the peak (a lowered peak): only later slots are free
+    "over the peak": (20, [4, 3], [1, 20, 64, 90], [1, 4], 6, [(70, 5), (130, 4), (1, 1)], []),
+    "kept ops": (20, [4, 3], [1, 20, 64, 90], [1, 4], 6, [(5, 2)],
+                 [(10, 75, 6), (200, 328, 3), (331, 332, 6)]),
+    **{f"n {n}": (n, [3, 2, 4, 1], list(range(1, 40)), [1, 3, 5], 8, [], [])
+       for n in (1, 15, 16, 17, 64, 65)},
+}
+
+
+@pytest.mark.parametrize("name", CASES)
+def test_decode_on_chip_edges(name):
+    """At the default slots, and at the last multiple of 64 slots that holds every schedule and
+    64 fewer, where the longest is redone off chip."""
+    _say("on-chip decode edges:", name)
+    inst = _instance(*CASES[name][:5], 41, *CASES[name][5:])
+    pop = W.random_population(43, 24, inst.n_active)
+    span = 0
+    for prio in pop:
+        _, s, m, _ = oracle.decode(inst, prio, want_schedule=True)
+        j, g = np.indices(s.shape)
+        span = max(span, int((s + np.asarray(inst.proc)[j, g, m]).max()))
+    full = -(-span // 64) * 64
+    for slots in sorted({0, full, max(full - 64, 64)}):
+        _compare(inst, pop, lds_slots=slots, schedule=slots != full)
