@@ -104,7 +104,8 @@ typedef struct {
 int ffs_prepare(ffs_instance *inst, void *workspace, size_t workspace_bytes, void *stream);
 
 /* Device workspace bytes for ffs_decode or ffs_decode_xy of `pop` chromosomes. lds_slots: the
- * power-profile slots kept on chip per chromosome (0 = library default);
+ * power-profile slots kept on chip per chromosome (0 = library default: 4096,
+ * or more, up to 32768, where that costs a population of this size no wave);
  * decodes that need more fall back to a slower profile in this workspace. */
 size_t ffs_decode_workspace_size(const ffs_instance *inst, int32_t pop, int32_t lds_slots);
 
@@ -180,7 +181,8 @@ typedef struct {
   int32_t islands, rows, cols;
   uint32_t pc, pm;
   int32_t mig_interval, mig_k;
-  int32_t lds_slots;                /* on-chip profile slots per decode, 0 = default (4096);
+  int32_t lds_slots;                /* on-chip profile slots per decode, 0 = default (4096, or
+                                       more, up to 32768, where that costs no wave);
                                        FFS_LDS_AUTO: sized by ga_init from generation 0 */
   int32_t encoding;                 /* 0: one priority per active job (n_genes = n_active);
                                        1: the paper's X/Y matrices (n_genes = 2 * n_ops, see

@@ -3133,6 +3133,46 @@ int resolve_cap(const ffs_instance *in, int32_t lds_slots) {
   return cap;
 }
 
+int compute_units() {
+  int dev = 0, v = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+    return 0;
+  return v;
+}
+
+// On-chip slots of pop decodes: as asked, or, where the caller leaves them to the
+// library, what resolve_cap takes (the workspace is laid out for that) or as many
+// more as cost no wave. A compute unit holds 16 waves of a decode (four a SIMD, by
+// their registers) and needs pop / compute units of them at once, so each may take
+// that share of its LDS, which is given out in pieces of 1280 bytes; past kChipSlots
+// the decoder would be the general one. A schedule that outgrows the slots costs a
+// second decode off chip, four times as long: the plan of an event (one decode of
+// 200 jobs, 10 stages and 4-6 machines, 6400 slots) and its reschedule take 1.90 ms
+// at 4096 slots and 0.75 ms at the 32768 that a lone decode gets. bytes(cap): LDS of
+// one decode.
+template <class F>
+int roomy_cap(const ffs_instance *in, int32_t lds_slots, int64_t pop, F bytes) {
+  const int base = resolve_cap(in, lds_slots);
+  const int cus = compute_units();
+  if (lds_slots > 0 || base >= in->horizon || cus < 1) return base;
+  int64_t waves = (pop + cus - 1) / cus;
+  waves = waves < 1 ? 1 : waves > 16 ? 16 : waves;
+  const int64_t room = max_lds_bytes() / waves / 1280 * 1280;
+  int64_t cap = (room - (int64_t)bytes(base) + base) / 64 * 64;
+  const int64_t h = (int64_t)align_up((size_t)in->horizon, 64);
+  if (cap > kChipSlots) cap = kChipSlots;
+  if (cap > h) cap = h;
+  return cap > base ? (int)cap : base;
+}
+int roomy_cap(const ffs_instance *in, int32_t lds_slots, int64_t pop, bool xy) {
+  if (xy)
+    return roomy_cap(in, lds_slots, pop, [&](int cap) {
+      return lds_bytes_xy(in->n_active, in->n_ops, in->n_stages, in->o_max, cap);
+    });
+  return roomy_cap(in, lds_slots, pop, [&](int cap) { return lds_bytes_of(in, cap); });
+}
+
 // Bytes of pack_kernel's table: n x g rows of omp words, then n due dates.
 size_t pq_bytes(int n, int g, int omp) {
   return align_up((size_t)n * g * omp * 4 + (size_t)n * 4 + 64, 256);
@@ -3317,7 +3357,9 @@ GaLayout ga_layout(void *ws, const ffs_instance *in, const ffs_ga_params *p, int
 // The on-chip slots a GA workspace layout is computed with: with FFS_LDS_AUTO
 // the slots are only known after generation 0, so the layout always holds the
 // off-chip profiles.
-int layout_cap(const ffs_ga_params *p, int cap) { return p->lds_slots == FFS_LDS_AUTO ? 0 : cap; }
+int layout_cap(const ffs_instance *in, const ffs_ga_params *p) {
+  return p->lds_slots == FFS_LDS_AUTO ? 0 : resolve_cap(in, p->lds_slots);
+}
 
 // On-chip slots FFS_LDS_AUTO works with: as many as one workgroup's LDS holds
 // next to the chromosome's arrays, at most `limit` and no more than the horizon
@@ -3610,7 +3652,7 @@ int ga_step_groups(ffs_ga *ga, const ffs_instance *in, const GaLayout &L, int32_
 template <int MAXM>
 int ga_step_impl(ffs_ga *ga, const ffs_instance *in, int32_t n_gen, hipStream_t stream,
                  const Screen *scr = nullptr) {
-  GaLayout L = ga_layout(ga->workspace, in, &ga->params, layout_cap(&ga->params, ga->lds_slots));
+  GaLayout L = ga_layout(ga->workspace, in, &ga->params, layout_cap(in, &ga->params));
   const DInst d = make_dinst(in, L.pq);
   const int pop = ga->pop, cap = ga->lds_slots, n = ga->n_genes;
   const int K = ga->params.rows * ga->params.cols;
@@ -3911,7 +3953,7 @@ int decode_job_vectors(const ffs_instance *inst, const int32_t *prio, int32_t po
       ((start == nullptr) != (mach == nullptr)))
     return FFS_E_INVAL;
   if (pop == 0) return FFS_OK;
-  const int cap = resolve_cap(inst, lds_slots);
+  int cap = resolve_cap(inst, lds_slots);
   if (lds_bytes(inst->n_active, cap) > (size_t)max_lds_bytes())
     return FFS_E_UNSUPPORTED;
   if (!workspace || workspace_bytes < decode_layout(nullptr, inst, pop, cap).total)
@@ -3924,6 +3966,7 @@ int decode_job_vectors(const ffs_instance *inst, const int32_t *prio, int32_t po
     return rc;
   }
   if ((rc = pack(inst, L.pq, s))) return rc;
+  cap = roomy_cap(inst, lds_slots, pop, false);
   switch (omp_of(inst->o_max)) {
     case 4:
       set_lds_limits<4>();
@@ -4088,7 +4131,7 @@ int ffs_decode_xy(const ffs_instance *inst, const int32_t *genes, int32_t pop, i
       (pop > 0 && (!obj || (!genes && inst->n_ops > 0))) || ((start == nullptr) != (mach == nullptr)))
     return FFS_E_INVAL;
   if (pop == 0) return FFS_OK;
-  const int cap = resolve_cap(inst, lds_slots);
+  int cap = resolve_cap(inst, lds_slots);
   if (lds_bytes_xy(inst->n_active, inst->n_ops, inst->n_stages, inst->o_max, cap) >
       (size_t)max_lds_bytes())
     return FFS_E_UNSUPPORTED;
@@ -4099,6 +4142,7 @@ int ffs_decode_xy(const ffs_instance *inst, const int32_t *genes, int32_t pop, i
   if ((rc = clear_header(L.hdr, s))) return rc;
   if ((rc = pack(inst, L.pq, s))) return rc;
   if ((rc = build_xy_table(inst, L.xyop, L.xyg0, s))) return rc;
+  cap = roomy_cap(inst, lds_slots, pop, true);
   switch (omp_of(inst->o_max)) {
     case 4:
       set_lds_limits<4>();
@@ -4128,8 +4172,7 @@ int ffs_status(void *workspace, void *stream) {
 
 size_t ffs_ga_workspace_size(const ffs_instance *inst, const ffs_ga_params *params) {
   if (check_host(inst) || check_ga_params(params) || inst->horizon < 1) return 0;
-  const int cap = resolve_cap(inst, params->lds_slots);
-  return ga_layout(nullptr, inst, params, layout_cap(params, cap)).total;
+  return ga_layout(nullptr, inst, params, layout_cap(inst, params)).total;
 }
 
 int ga_init(ffs_ga *ga, const ffs_instance *inst, const ffs_ga_params *params, uint64_t seed,
@@ -4140,7 +4183,7 @@ int ga_init(ffs_ga *ga, const ffs_instance *inst, const ffs_ga_params *params, u
   if ((rc = check_ga_params(params))) return rc;
   const bool auto_cap = params->lds_slots == FFS_LDS_AUTO;
   if (auto_cap && params->encoding != 0) return FFS_E_UNSUPPORTED;
-  const int cap = auto_cap ? probe_cap(inst) : resolve_cap(inst, params->lds_slots);
+  int cap = auto_cap ? probe_cap(inst) : resolve_cap(inst, params->lds_slots);
   const size_t lds = params->encoding == 1
                          ? lds_bytes_xy(inst->n_active, inst->n_ops, inst->n_stages, inst->o_max, cap)
                          : lds_bytes(inst->n_active, cap);
@@ -4151,6 +4194,7 @@ int ga_init(ffs_ga *ga, const ffs_instance *inst, const ffs_ga_params *params, u
   ga->params = *params;
   ga->n_genes = (int32_t)chrom_len(inst, params);
   ga->pop = params->islands * params->rows * params->cols;
+  if (!auto_cap) cap = roomy_cap(inst, params->lds_slots, ga->pop, params->encoding == 1);
   ga->seed = seed;
   ga->shop = shop;
   ga->event = event;
@@ -4164,7 +4208,7 @@ int ga_init(ffs_ga *ga, const ffs_instance *inst, const ffs_ga_params *params, u
   ga->n_jobs = inst->n_jobs;
   ga->horizon = inst->horizon;
   hipStream_t s = (hipStream_t)stream;
-  GaLayout L = ga_layout(workspace, inst, params, layout_cap(params, cap));
+  GaLayout L = ga_layout(workspace, inst, params, layout_cap(inst, params));
   for (int k = 0; k < 2; ++k) {
     ga->prio[k] = L.prio[k];
     ga->obj[k] = L.obj[k];

@@ -8,7 +8,7 @@ import pytest
 
 import oracle
 from paper_1903_10741_amd import workloads as W
-from test_gpu_decode import _compare, _say
+from test_gpu_decode import _compare, _ffs, _say
 
 pytestmark = pytest.mark.gpu
 
@@ -60,3 +60,25 @@ def test_decode_on_chip_edges(name):
     full = -(-span // 64) * 64
     for slots in sorted({0, full, max(full - 64, 64)}):
         _compare(inst, pop, lds_slots=slots, schedule=slots != full)
+
+
+@pytest.mark.parametrize("kind,pop", [("job", 3), ("job", 700), ("job", 4200), ("fifo", 5), ("xy", 5)])
+def test_decode_default_slots(kind, pop):
+    """Schedules of 5000 to 8000 slots at the default slots, which grow with the LDS that a
+    population leaves each decode: one population a compute unit holds alone, one of a few waves
+    a unit and one of more than the chip holds at once; the FIFO rules; X/Y chromosomes."""
+    torch, ffsga = _ffs()
+    _say("default slots,", kind, "pop", pop)
+    inst = W.random_instance(29, n_jobs=50, n_stages=3, machines=[2, 2, 1], p_max=150, percent=60)
+    inst.decode_rules = 1 if kind == "fifo" else 0
+    d = ffsga.DeviceInstance.from_host(inst)
+    xy = kind == "xy"
+    prio = W.random_xy_population(31, pop, inst) if xy else W.random_population(31, pop, inst.n_active)
+    got = ffsga.ffs_decode(d, torch.from_numpy(prio).cuda(), xy=xy).cpu().numpy()
+    want = oracle.decode_xy_pop(inst, prio) if xy else oracle.decode_pop(inst, prio, n_threads=8)
+    assert (got == want).all()
+    if kind == "job":
+        gp = W.GaParams(1, 1, pop, mig_interval=0, mig_k=0)
+        ga = ffsga.GA(d, ffsga.GaConfig.of(gp), 5, 0, 0)
+        assert ga.ga.lds_slots > 4096 and ga.overflows() == 0
+        assert (ga.view()["obj"].cpu().numpy() == oracle.ga_init(inst, gp, 5, 0, 0)["obj"]).all()
