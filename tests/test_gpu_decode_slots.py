@@ -82,3 +82,21 @@ def test_decode_default_slots(kind, pop):
         ga = ffsga.GA(d, ffsga.GaConfig.of(gp), 5, 0, 0)
         assert ga.ga.lds_slots > 4096 and ga.overflows() == 0
         assert (ga.view()["obj"].cpu().numpy() == oracle.ga_init(inst, gp, 5, 0, 0)["obj"]).all()
+
+
+@pytest.mark.parametrize("pop", [2048, 2049, 2200])
+def test_auto_slots_in_two_parts(pop):
+    """FFS_LDS_AUTO on either side of the population from which generation 0 is decoded in two
+    parts (4 waves on each of 256 compute units, twice): state and a generation equal the oracle's."""
+    torch, ffsga = _ffs()
+    _say("auto slots, pop", pop)
+    inst = W.random_instance(37, n_jobs=40, n_stages=3, machines=[2, 2, 1], p_max=150, percent=60)
+    gp = W.GaParams(1, 1, pop, mig_interval=0, mig_k=0)
+    ga = ffsga.GA(ffsga.DeviceInstance.from_host(inst),
+                  ffsga.GaConfig.of(gp, lds_slots=ffsga.FFS_LDS_AUTO), 5, 0, 0)
+    assert (ga.view()["obj"].cpu().numpy() == oracle.ga_init(inst, gp, 5, 0, 0, n_threads=8)["obj"]).all()
+    ga.step(1)
+    ga.status()
+    st = oracle.ga_run(inst, gp, 5, 0, 0, 1, n_threads=8)
+    for k in ("prio", "obj", "elite", "elite_obj"):
+        assert (ga.view()[k].cpu().numpy() == np.asarray(st[k])).all(), k
