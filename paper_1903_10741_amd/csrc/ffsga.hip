@@ -1490,6 +1490,40 @@ __device__ void wave_arg(int64_t &v, int &idx) {
   }
 }
 
+// Block-wide (value, index) reductions with the lowest index on ties.
+// sv, si: a slot for each wave.
+template <bool MAX>
+__device__ void block_arg(int64_t v, int idx, int64_t *sv, int *si, int64_t &out_v, int &out_i) {
+  const int lane = __lane_id(), wave = threadIdx.x / kWave, waves = blockDim.x / kWave;
+  wave_arg<MAX>(v, idx);
+  if (lane == 0) {
+    sv[wave] = v;
+    si[wave] = idx;
+  }
+  __syncthreads();
+  out_v = lane < waves ? sv[lane] : MAX ? LLONG_MIN : LLONG_MAX;
+  out_i = lane < waves ? si[lane] : INT_MAX;
+  wave_arg<MAX>(out_v, out_i);
+  __syncthreads();
+}
+
+template <bool MAX>
+__device__ void island_arg(const int64_t *obj, int base, int K, const uint8_t *taken, int64_t *sv,
+                           int *si, int64_t &out_v, int &out_i) {
+  int64_t bv = MAX ? LLONG_MIN : LLONG_MAX;
+  int bi = INT_MAX;
+#pragma unroll 4
+  for (int k = threadIdx.x; k < K; k += blockDim.x) {
+    if (taken && taken[k]) continue;
+    const int64_t o = obj[base + k];
+    if (MAX ? (o > bv || (o == bv && k < bi)) : (o < bv || (o == bv && k < bi))) {
+      bv = o;
+      bi = k;
+    }
+  }
+  block_arg<MAX>(bv, bi, sv, si, out_v, out_i);
+}
+
 // Replacement of island I by one wave (same rule as replace_island): the best
 // child becomes the best-in-history if it beats it, and the best-in-history
 // replaces the worst child. The genes kept are read once and stored to both
@@ -1534,53 +1568,58 @@ __device__ void replace_island_wave(const GaDev &A, int I, int K, int n) {
 // neighbourhood, replace if better).
 // ---------------------------------------------------------------------------
 // E_max of eq. (13): 10^a, the least a >= 1 above every objective of generation 0.
-__global__ __launch_bounds__(256) void emax_kernel(const int64_t *obj, int pop, Header *h) {
-  __shared__ int64_t sh[256];
-  const int t = threadIdx.x;
-  int64_t m = LLONG_MIN;
-  for (int i = t; i < pop; i += 256) m = max(m, obj[i]);
-  sh[t] = m;
-  __syncthreads();
-  for (int w = 128; w >= 1; w >>= 1) {
-    if (t < w) sh[t] = max(sh[t], sh[t + w]);
-    __syncthreads();
-  }
-  if (t == 0) {
+__global__ __launch_bounds__(1024) void emax_kernel(const int64_t *obj, int pop, Header *h) {
+  __shared__ int64_t sv[16];
+  __shared__ int si[16];
+  int64_t m;
+  int i;
+  island_arg<true>(obj, 0, pop, nullptr, sv, si, m, i);
+  if (threadIdx.x == 0) {
     int64_t e = 10;
-    while (!(sh[0] < e) && e <= LLONG_MAX / 10) e *= 10;
+    while (!(m < e) && e <= LLONG_MAX / 10) e *= 10;
     h->e_max = e;
   }
 }
 
 // Running sums of eq. (13)'s fitness F_i = max(E_max - obj_i, 0) in index
-// order (integers: any order of additions gives the same sums). Thread t of
-// one block of 1024 sums a run of consecutive entries; the runs' totals are
-// scanned and each run then writes its running sums.
-__global__ __launch_bounds__(1024) void fitness_scan_kernel(const int64_t *obj, int pop,
-                                                            const Header *h, u64 *prefix) {
-  __shared__ u64 part[1024];
-  const int t = threadIdx.x;
+// order (integers: any order of additions gives the same sums). One block: each
+// of its 16 waves takes a run of 64-entry rows, sums them, and from the sums of
+// the waves before it writes its running sums, a scan of a row at a time. Bound by
+// latency (16384 entries are 256 KB of traffic), so rows are read whole and
+// several at once: 31 -> 13.3 us for 16384 entries.
+constexpr int kScanWaves = 16;
+__global__ __launch_bounds__(kScanWaves *kWave) void fitness_scan_kernel(const int64_t *obj, int pop,
+                                                                         const Header *h,
+                                                                         u64 *prefix) {
+  __shared__ u64 part[kScanWaves];
+  const int lane = __lane_id(), wave = threadIdx.x / kWave;
   const int64_t e = h->e_max;
-  const int c = (pop + 1023) / 1024;
-  const int a = min(t * c, pop), b = min(a + c, pop);
+  const int rows = (pop + kWave - 1) / kWave, c = (rows + kScanWaves - 1) / kScanWaves;
+  const int a = min(wave * c, rows), b = min(a + c, rows);
+  auto fitness = [&](int row) {
+    const int i = row * kWave + lane;
+    const int64_t f = i < pop ? e - obj[i] : 0;
+    return f > 0 ? (u64)f : 0ull;
+  };
   u64 sum = 0;
-  for (int i = a; i < b; ++i) {
-    const int64_t f = e - obj[i];
-    sum += f > 0 ? (u64)f : 0ull;
-  }
-  part[t] = sum;
+#pragma unroll 8
+  for (int r = a; r < b; ++r) sum += fitness(r);
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, kWave);
+  if (lane == 0) part[wave] = sum;
   __syncthreads();
-  for (int d = 1; d < 1024; d <<= 1) {
-    const u64 v = t >= d ? part[t - d] : 0ull;
-    __syncthreads();
-    part[t] += v;
-    __syncthreads();
-  }
-  u64 run = t > 0 ? part[t - 1] : 0ull;
-  for (int i = a; i < b; ++i) {
-    const int64_t f = e - obj[i];
-    run += f > 0 ? (u64)f : 0ull;
-    prefix[i] = run;
+  u64 run = 0;
+  for (int w = 0; w < wave; ++w) run += part[w];
+#pragma unroll 4
+  for (int r = a; r < b; ++r) {
+    u64 v = fitness(r);
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+      const u64 o = __shfl_up(v, d, kWave);
+      v += lane >= d ? o : 0ull;
+    }
+    if (r * kWave + lane < pop) prefix[r * kWave + lane] = run + v;
+    run += readlane64(v, kWave - 1);
   }
 }
 
@@ -1667,22 +1706,18 @@ __global__ __launch_bounds__(64) void cellular_accept_kernel(const int32_t *prio
 }
 
 // Best in history of a whole population (lowest objective, lowest slot on ties).
-__global__ __launch_bounds__(64) void elite_update_kernel(const int32_t *prio, const int64_t *obj,
-                                                          int32_t *elite, int64_t *elite_obj,
-                                                          int pop, int n) {
-  int64_t bv = LLONG_MAX;
-  int b = INT_MAX;
-  for (int k = __lane_id(); k < pop; k += kWave) {
-    const int64_t o = obj[k];
-    if (o < bv) {
-      bv = o;
-      b = k;
-    }
-  }
-  wave_arg<false>(bv, b);
+__global__ __launch_bounds__(1024) void elite_update_kernel(const int32_t *prio, const int64_t *obj,
+                                                            int32_t *elite, int64_t *elite_obj,
+                                                            int pop, int n) {
+  __shared__ int64_t sv[16];
+  __shared__ int si[16];
+  int64_t bv;
+  int b;
+  island_arg<false>(obj, 0, pop, nullptr, sv, si, bv, b);
   if (bv < elite_obj[0]) {
-    for (int k = __lane_id(); k < n; k += kWave) elite[k] = prio[(size_t)b * n + k];
-    if (__lane_id() == 0) elite_obj[0] = bv;
+    for (int k = threadIdx.x; k < n; k += blockDim.x) elite[k] = prio[(size_t)b * n + k];
+    __syncthreads();
+    if (threadIdx.x == 0) elite_obj[0] = bv;
   }
 }
 
@@ -2318,46 +2353,6 @@ __global__ __launch_bounds__(64) void ga_screened_kernel(DInst I, GaDev A, int g
   });
 }
 
-// Block-wide (value, index) reductions with the lowest index on ties.
-template <bool MAX>
-__device__ void block_arg(int64_t v, int idx, int64_t *sv, int *si, int64_t &out_v, int &out_i) {
-  const int t = threadIdx.x;
-  sv[t] = v;
-  si[t] = idx;
-  __syncthreads();
-  for (int h = blockDim.x / 2; h > 0; h >>= 1) {
-    if (t < h) {
-      const int64_t a = sv[t], b = sv[t + h];
-      const int ia = si[t], ib = si[t + h];
-      const bool take_b = MAX ? (b > a || (b == a && ib < ia)) : (b < a || (b == a && ib < ia));
-      if (take_b) {
-        sv[t] = b;
-        si[t] = ib;
-      }
-    }
-    __syncthreads();
-  }
-  out_v = sv[0];
-  out_i = si[0];
-  __syncthreads();
-}
-
-template <bool MAX>
-__device__ void island_arg(const int64_t *obj, int base, int K, const uint8_t *taken, int64_t *sv,
-                           int *si, int64_t &out_v, int &out_i) {
-  int64_t bv = MAX ? LLONG_MIN : LLONG_MAX;
-  int bi = INT_MAX;
-  for (int k = threadIdx.x; k < K; k += blockDim.x) {
-    if (taken && taken[k]) continue;
-    const int64_t o = obj[base + k];
-    if (MAX ? (o > bv || (o == bv && k < bi)) : (o < bv || (o == bv && k < bi))) {
-      bv = o;
-      bi = k;
-    }
-  }
-  block_arg<MAX>(bv, bi, sv, si, out_v, out_i);
-}
-
 // Elitist replacement (Section 4.4): the island's best child refreshes the
 // best-in-history, which then overwrites the island's worst child.
 __device__ void replace_island(int32_t *prio, int64_t *obj, int32_t *elite, int64_t *elite_obj,
@@ -2391,11 +2386,20 @@ __global__ __launch_bounds__(64) void replace_wave_kernel(int32_t *prio, int64_t
   replace_island_wave(A, blockIdx.x, K, n);
 }
 
-__global__ __launch_bounds__(256) void elite_init_kernel(const int32_t *prio, const int64_t *obj,
+// The same by a block per island.
+__global__ __launch_bounds__(1024) void replace_block_kernel(int32_t *prio, int64_t *obj,
+                                                             int32_t *elite, int64_t *elite_obj,
+                                                             int K, int n) {
+  __shared__ int64_t sv[16];
+  __shared__ int si[16];
+  replace_island(prio, obj, elite, elite_obj, blockIdx.x, K, n, sv, si);
+}
+
+__global__ __launch_bounds__(1024) void elite_init_kernel(const int32_t *prio, const int64_t *obj,
                                                          int32_t *elite, int64_t *elite_obj, int K,
                                                          int n) {
-  __shared__ int64_t sv[256];
-  __shared__ int si[256];
+  __shared__ int64_t sv[16];
+  __shared__ int si[16];
   const int I = blockIdx.x, base = I * K;
   int64_t bv;
   int b;
@@ -2458,8 +2462,8 @@ __device__ void migrate_apply_island(int32_t *prio, int64_t *obj, int32_t *elite
 __global__ __launch_bounds__(256) void migrate_collect_kernel(const int32_t *prio, const int64_t *obj,
                                                               int32_t *stage_prio, int64_t *stage_obj,
                                                               int K, int n, int mig_k) {
-  __shared__ int64_t sv[256];
-  __shared__ int si[256];
+  __shared__ int64_t sv[4];
+  __shared__ int si[4];
   extern __shared__ uint8_t taken[];
   migrate_collect_island(prio, obj, stage_prio, stage_obj, blockIdx.x, K, n, mig_k, taken, sv, si);
 }
@@ -2469,8 +2473,8 @@ __global__ __launch_bounds__(256) void migrate_apply_kernel(int32_t *prio, int64
                                                             const int32_t *stage_prio,
                                                             const int64_t *stage_obj, int K, int n,
                                                             int mig_k, int islands) {
-  __shared__ int64_t sv[256];
-  __shared__ int si[256];
+  __shared__ int64_t sv[4];
+  __shared__ int si[4];
   extern __shared__ uint8_t taken[];
   migrate_apply_island(prio, obj, elite, elite_obj, stage_prio, stage_obj, blockIdx.x, K, n, mig_k,
                        islands, taken, sv, si);
@@ -2479,8 +2483,8 @@ __global__ __launch_bounds__(256) void migrate_apply_kernel(int32_t *prio, int64
 __global__ __launch_bounds__(256) void best_kernel(const int32_t *elite, const int64_t *elite_obj,
                                                    int islands, int n, int32_t *prio_out,
                                                    int64_t *obj_out) {
-  __shared__ int64_t sv[256];
-  __shared__ int si[256];
+  __shared__ int64_t sv[4];
+  __shared__ int si[4];
   int64_t bv = LLONG_MAX;
   int bi = INT_MAX;
   for (int k = threadIdx.x; k < islands; k += blockDim.x)
@@ -2651,8 +2655,8 @@ __global__ __launch_bounds__(64) void batch_class_kernel(BatchArgs B, int d, int
 }
 
 __global__ __launch_bounds__(256) void batch_replace_kernel(BatchArgs B) {
-  __shared__ int64_t sv[256];
-  __shared__ int si[256];
+  __shared__ int64_t sv[4];
+  __shared__ int si[4];
   const int d = blockIdx.x / B.islands, I = blockIdx.x % B.islands;
   const BatchSlot S = ld_const_struct(B.slots + d);
   if (!S.active) return;
@@ -2665,8 +2669,8 @@ __device__ __forceinline__ bool migrates(const BatchArgs &B, int gen) {
 }
 
 __global__ __launch_bounds__(256) void batch_migrate_collect_kernel(BatchArgs B) {
-  __shared__ int64_t sv[256];
-  __shared__ int si[256];
+  __shared__ int64_t sv[4];
+  __shared__ int si[4];
   extern __shared__ uint8_t taken[];
   const int d = blockIdx.x / B.islands, I = blockIdx.x % B.islands;
   const BatchSlot S = ld_const_struct(B.slots + d);
@@ -2677,8 +2681,8 @@ __global__ __launch_bounds__(256) void batch_migrate_collect_kernel(BatchArgs B)
 }
 
 __global__ __launch_bounds__(256) void batch_migrate_apply_kernel(BatchArgs B) {
-  __shared__ int64_t sv[256];
-  __shared__ int si[256];
+  __shared__ int64_t sv[4];
+  __shared__ int si[4];
   extern __shared__ uint8_t taken[];
   const int d = blockIdx.x / B.islands, I = blockIdx.x % B.islands;
   const BatchSlot S = ld_const_struct(B.slots + d);
@@ -3464,6 +3468,10 @@ int waves_per_cu(size_t bytes) {
   return b;
 }
 
+// Threads of a block that goes once over K objectives: enough waves to have them all
+// in flight, 256 threads at most where K is that small.
+dim3 block_of(int K) { return dim3(K >= 1024 ? 1024 : 256); }
+
 template <int MAXM>
 int ga_init_impl(ffs_ga *ga, const ffs_instance *in, const GaLayout &L, hipStream_t stream,
                  bool auto_cap) {
@@ -3523,12 +3531,12 @@ int ga_init_impl(ffs_ga *ga, const ffs_instance *in, const GaLayout &L, hipStrea
       return FFS_E_DEVICE;
     if ((rc = ga_overflow<MAXM>(in, L, 0, cap0, stream, false, span))) return rc;
   }
-  if (launch(-1, elite_init_kernel, dim3(ga->params.islands), dim3(256), 0, stream,
+  if (launch(-1, elite_init_kernel, dim3(ga->params.islands), block_of(K), 0, stream,
              (const int32_t *)L.prio[0], (const int64_t *)L.obj[0], L.elite, L.elite_obj, K,
              n) != hipSuccess)
     return FFS_E_DEVICE;
   if (ga->params.scheme == FFS_GA_CLASSICAL &&
-      launch(-1, emax_kernel, dim3(1), dim3(256), 0, stream, (const int64_t *)L.obj[0], pop,
+      launch(-1, emax_kernel, dim3(1), block_of(pop), 0, stream, (const int64_t *)L.obj[0], pop,
              L.hdr) != hipSuccess)
     return FFS_E_DEVICE;
   return auto_cap ? size_slots(&ga->lds_slots) : FFS_OK;
@@ -3730,7 +3738,7 @@ int ga_step_impl(ffs_ga *ga, const ffs_instance *in, int32_t n_gen, hipStream_t 
       if (launch(2, cellular_accept_kernel, dim3(pop), dim3(kWave), 0, stream,
                  (const int32_t *)L.prio[cur], (const int64_t *)L.obj[cur], L.prio[1 - cur],
                  L.obj[1 - cur], n) != hipSuccess ||
-          launch(2, elite_update_kernel, dim3(1), dim3(kWave), 0, stream,
+          launch(2, elite_update_kernel, dim3(1), block_of(pop), 0, stream,
                  (const int32_t *)L.prio[1 - cur], (const int64_t *)L.obj[1 - cur], L.elite,
                  L.elite_obj, pop, n) != hipSuccess)
         return FFS_E_DEVICE;
@@ -3738,8 +3746,15 @@ int ga_step_impl(ffs_ga *ga, const ffs_instance *in, int32_t n_gen, hipStream_t 
       ga->generation = gen;
       continue;
     }
-    if (launch(2, replace_wave_kernel, dim3(ga->params.islands), dim3(kWave), 0, stream,
-               L.prio[1 - cur], L.obj[1 - cur], L.elite, L.elite_obj, K, n) != hipSuccess)
+    // One wave an island reads its objectives 64 at a time, which is the longer way from
+    // about 1000 on (one island of 512: 5.9 us against 6.8 by a block; 1024: 8.8 and 7.7;
+    // 16384: 73.6 and 15.5). Island groups keep the wave: a block of 16 waits for that
+    // many free places on a compute unit the other groups' decodes fill (8 islands of
+    // 4096: 39 us and 76).
+    const bool block = K >= 1024;
+    if (launch(2, block ? replace_block_kernel : replace_wave_kernel, dim3(ga->params.islands),
+               block ? block_of(K) : dim3(kWave), 0, stream, L.prio[1 - cur], L.obj[1 - cur], L.elite,
+               L.elite_obj, K, n) != hipSuccess)
       return FFS_E_DEVICE;
     if (migrates(ga->params, gen) && !migrate(ga->params, L, cur, n, stream))
       return FFS_E_DEVICE;
@@ -3958,7 +3973,7 @@ int batch_init_launch(const ffs_batch *b, const BatchArgs &B, int slot, const Ba
     return FFS_E_DEVICE;
   uint8_t *base = L.slot_base + L.slot_stride * slot;
   const int n = b->n_genes[slot];
-  if (launch(-1, elite_init_kernel, dim3(p.ga.islands), dim3(256), 0, s,
+  if (launch(-1, elite_init_kernel, dim3(p.ga.islands), block_of(p.ga.rows * p.ga.cols), 0, s,
              (const int32_t *)(base + L.off_prio[0]), (const int64_t *)(base + L.off_obj[0]),
              (int32_t *)(base + L.off_elite), (int64_t *)(base + L.off_eobj),
              p.ga.rows * p.ga.cols, n) != hipSuccess)
