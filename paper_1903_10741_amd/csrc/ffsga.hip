@@ -2323,6 +2323,44 @@ __global__ __launch_bounds__(64) void sg_score_kernel(const float *table, const 
   if (__lane_id() == 0) y[blockIdx.x] = s;
 }
 
+// The same for a large count, with the table in LDS: a wave's 64 gathers then meet only
+// in LDS banks, where each of the other kernel's reads a line of the L2 for 4 bytes of
+// it. A block scores kScoreBlock chromosomes, kScoreWave a wave, 64 genes of each at a
+// time against the 64 rows of the table that these take; lane partials run on from
+// one 64 to the next, so the sums and their order are the same.
+constexpr int kScoreWaves = 16, kScoreWave = 8, kScoreBlock = kScoreWaves * kScoreWave;
+__global__ __launch_bounds__(kScoreWaves *kWave) void sg_score_block_kernel(
+    const float *table, const float *theta, int n, const int32_t *prio, int count, float *y) {
+  extern __shared__ __align__(16) float slab[];  // 64 rows of n
+  const int lane = __lane_id(), first = blockIdx.x * kScoreBlock + (threadIdx.x / kWave) * kScoreWave;
+  float s[kScoreWave] = {};
+  uint32_t bad = 0;
+  for (int k0 = 0; k0 < n; k0 += kWave) {
+    const int k = k0 + lane, rows = min(n - k0, kWave);
+    int v[kScoreWave];
+#pragma unroll
+    for (int c = 0; c < kScoreWave; ++c)
+      v[c] = k < n && first + c < count ? prio[(size_t)(first + c) * n + k] : 1;
+    __syncthreads();
+    for (int i = threadIdx.x; i < rows * n; i += blockDim.x) slab[i] = table[(size_t)k0 * n + i];
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < kScoreWave; ++c) {
+      const bool ok = v[c] >= 1 && v[c] <= n;
+      bad |= ok ? 0u : 1u << c;
+      if (k < n) s[c] += slab[lane * n + (ok ? v[c] - 1 : 0)];
+    }
+  }
+  const float b3 = theta[FFS_SG_PARAMS - 1];
+#pragma unroll
+  for (int c = 0; c < kScoreWave; ++c) {
+    for (int off = 32; off > 0; off >>= 1) s[c] += __shfl_xor(s[c], off);
+    const bool nan = ballot64(bad >> c & 1) != 0;
+    if (lane == 0 && first + c < count)
+      y[first + c] = nan ? __builtin_nanf("") : __fadd_rn(b3, __fdiv_rn(s[c], (float)n));
+  }
+}
+
 // Screened generation: every cell breeds V candidate children, keeps the one
 // with the lowest surrogate score (lowest v on ties), stores and decodes it.
 template <int MAXM>
@@ -4311,15 +4349,24 @@ int ga_set_island_groups(int32_t groups) {
   return group_streams(&GS);
 }
 
+constexpr int kScoreMany = 32768;
 int sg_score(const ffs_surrogate *model, const float *table, int32_t n_genes, const int32_t *prio,
              int32_t count, float *y, void *stream) {
   if (!model || !model->theta || !table || !prio || !y || n_genes < 1 ||
       n_genes > FFS_SG_MAX_GENES || count < 0)
     return FFS_E_INVAL;
-  if (launch(-1, sg_score_kernel, dim3(count), dim3(kWave), 0, (hipStream_t)stream, table,
-             (const float *)model->theta, n_genes, prio, y) != hipSuccess)
-    return FFS_E_DEVICE;
-  return FFS_OK;
+  hipStream_t s = (hipStream_t)stream;
+  const float *theta = model->theta;
+  // From 32768 on the blocks fill the chip and win at every n (65536: 52.2 -> 26.2 us at
+  // 200 genes, 17.2 -> 9.8 at 50; 32768: 26.4 -> 15.5 and 9.8 -> 9.7); at 16384 of 256
+  // genes they take 21.2 us where a wave a chromosome takes 17.9.
+  const hipError_t e =
+      count >= kScoreMany
+          ? launch(-1, sg_score_block_kernel, dim3((count + kScoreBlock - 1) / kScoreBlock),
+                   dim3(kScoreWaves * kWave), (size_t)4 * kWave * n_genes, s, table, theta, n_genes,
+                   prio, count, y)
+          : launch(-1, sg_score_kernel, dim3(count), dim3(kWave), 0, s, table, theta, n_genes, prio, y);
+  return e == hipSuccess ? FFS_OK : FFS_E_DEVICE;
 }
 
 int ga_step_screened(ffs_ga *ga, const ffs_instance *inst, const ffs_surrogate *model,

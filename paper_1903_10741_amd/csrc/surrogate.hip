@@ -136,38 +136,33 @@ __device__ __forceinline__ int acc_col() {
 // ---------------------------------------------------------------------------
 // Features, layer-1 constants, bf16 copies.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void features_kernel(ffs_instance in, float *feats) {
-  __shared__ int32_t smax[256];
+// One block. The least processing times of a job's unfrozen stages are added in LDS, a
+// thread each (whole numbers: any order gives the same sum), so that the loads of all
+// stages are in flight at once: 14.7 -> 7.4 us for 200 jobs of 10 stages.
+__global__ __launch_bounds__(1024) void features_kernel(ffs_instance in, float *feats) {
+  __shared__ unsigned long long sum[FFS_SG_MAX_GENES];
+  __shared__ int32_t smax;
   const int n = in.n_active, g = in.n_stages, om = in.o_max;
-  int32_t my_max = 0;
-  for (int k = threadIdx.x; k < n; k += blockDim.x) {
-    const int j = in.active[k];
-    int32_t tot = 0;
-    for (int s = in.first_stage[j]; s < g; ++s) {
-      const int32_t *row = in.proc + ((size_t)j * g + s) * om;
-      int32_t best = row[0];
-      for (int m = 1; m < in.n_machines[s]; ++m) best = row[m] < best ? row[m] : best;
-      tot += best;
-    }
-    my_max = tot > my_max ? tot : my_max;
-  }
-  smax[threadIdx.x] = my_max;
+  for (int k = threadIdx.x; k < n; k += blockDim.x) sum[k] = 0;
+  if (threadIdx.x == 0) smax = 0;
   __syncthreads();
-  for (int h = 128; h > 0; h >>= 1) {
-    if ((int)threadIdx.x < h && smax[threadIdx.x + h] > smax[threadIdx.x])
-      smax[threadIdx.x] = smax[threadIdx.x + h];
-    __syncthreads();
+  for (int i = threadIdx.x; i < n * g; i += blockDim.x) {
+    const int k = i / g, s = i % g, j = in.active[k];
+    if (s < in.first_stage[j]) continue;
+    const int32_t *row = in.proc + ((size_t)j * g + s) * om;
+    const int nm = in.n_machines[s];
+    int32_t best = row[0];
+#pragma unroll 4
+    for (int m = 1; m < nm; ++m) best = row[m] < best ? row[m] : best;
+    atomicAdd(&sum[k], (unsigned long long)(int64_t)best);
   }
-  const float scale = (float)(smax[0] > 1 ? smax[0] : 1);
+  __syncthreads();
+  for (int k = threadIdx.x; k < n; k += blockDim.x) atomicMax(&smax, (int32_t)sum[k]);
+  __syncthreads();
+  const float scale = (float)(smax > 1 ? smax : 1);
   for (int k = threadIdx.x; k < n; k += blockDim.x) {
     const int j = in.active[k];
-    int64_t tot = 0;
-    for (int s = in.first_stage[j]; s < g; ++s) {
-      const int32_t *row = in.proc + ((size_t)j * g + s) * om;
-      int32_t best = row[0];
-      for (int m = 1; m < in.n_machines[s]; ++m) best = row[m] < best ? row[m] : best;
-      tot += best;
-    }
+    const int64_t tot = (int64_t)sum[k];
     const int64_t ready = in.ready[j];
     const int64_t start = ready > in.rs ? ready : in.rs;
     const int64_t slack = (int64_t)in.due[j] - start - tot;
@@ -747,7 +742,7 @@ int sg_features(const ffs_instance *inst, float *feats, void *workspace, size_t 
       inst->n_stages < 1 || inst->o_max < 1 || !inst->active || !inst->proc ||
       !inst->n_machines || !inst->first_stage || !inst->ready || !inst->due)
     return FFS_E_INVAL;
-  hipLaunchKernelGGL(features_kernel, dim3(1), dim3(256), 0, (hipStream_t)stream, *inst, feats);
+  hipLaunchKernelGGL(features_kernel, dim3(1), dim3(1024), 0, (hipStream_t)stream, *inst, feats);
   return ok(hipGetLastError()) ? FFS_OK : FFS_E_DEVICE;
 }
 

@@ -43,3 +43,23 @@ def test_train_step_sizes(n, B):
             bt[-1] = np.inf
         m.train_step(feats, torch.from_numpy(bp), torch.from_numpy(bt), 1e-3)
         assert torch.equal(m.theta, before)
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 256])
+def test_scores_of_a_large_count_keep_their_bits(n):
+    """32767 chromosomes are scored one a wave, 32768 and more in blocks of 128 with the table in
+    LDS: each gets the same bits from both, invalid genes a NaN, and no score is written past the
+    count."""
+    torch, ffsga = _ffs()
+    _say("scores of a large count, n", n)
+    th, _ = _params(n)
+    m = ffsga.Surrogate(th)
+    inst = W.random_instance(n, n_jobs=n, n_stages=2, machines=2, p_max=9)
+    table = m.score_table(m.features(ffsga.DeviceInstance.from_host(inst)), n)
+    count = 32768 + 131
+    prio = torch.from_numpy(W.random_population(n, count, n)).cuda()
+    prio[[5, 130, count - 1], [0, n // 2, n - 1]] = torch.tensor([0, n + 1, -7], dtype=torch.int32).cuda()
+    want = torch.cat([m.score(table, prio[:20000]), m.score(table, prio[20000:])])
+    got = m.score(table, prio)
+    assert torch.equal(got.view(torch.int32), want.view(torch.int32))
+    assert torch.isnan(got).sum() == 3
