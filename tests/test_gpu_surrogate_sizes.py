@@ -63,3 +63,15 @@ def test_scores_of_a_large_count_keep_their_bits(n):
     got = m.score(table, prio)
     assert torch.equal(got.view(torch.int32), want.view(torch.int32))
     assert torch.isnan(got).sum() == 3
+
+
+@pytest.mark.parametrize("count,group", [(1, 1), (300, 255), (513, 257), (4096, 4096), (8193, 4096),
+                                         (4097, 4097), (9000, 9000)])
+def test_targets_sizes(count, group):
+    """Groups on either side of the 256 runs and of the 4096 entries whose logarithms are kept."""
+    torch, ffsga = _ffs()
+    _say("targets of", count, "in groups of", group)
+    obj = np.random.default_rng(count).integers(1, 10**6, size=count).astype(np.int64)
+    got = ffsga.Surrogate(W.surrogate_init(0)).targets(torch.from_numpy(obj), group)
+    want = S.targets(obj, group)
+    assert (np.abs(got.cpu().numpy().astype(np.float64) - want) <= S.U32 * np.abs(want) + 1e-9).all()
