@@ -4241,6 +4241,9 @@ int ffs_status(void *workspace, void *stream) {
   Header host;
   int rc = read_header((Header *)workspace, &host, s);
   if (rc) return rc;
+  // Nothing flagged: nothing to clear (the copy and its wait are as long as the read:
+  // the plan of a shop of 10 jobs 68 -> 54 us, one decode and its status).
+  if (host.err == 0) return FFS_OK;
   const int32_t zero = 0;
   if (hipMemcpyAsync(&((Header *)workspace)->err, &zero, sizeof(zero), hipMemcpyHostToDevice, s) !=
           hipSuccess ||
