@@ -8,7 +8,8 @@ ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libffsga.so")
 SRCS = [os.path.join(HERE, "csrc", f) for f in ("ffsga.hip", "surrogate.hip")]
 INCLUDE = os.path.join(ROOT, "include")
-HEADERS = [os.path.join(INCLUDE, f) for f in ("ffsga.h", "ffs_surrogate.h")]
+HEADERS = [*(os.path.join(INCLUDE, f) for f in ("ffsga.h", "ffs_surrogate.h")),
+           os.path.join(HERE, "csrc", "lds_sizes.h")]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -18,7 +19,7 @@ HIPCC_FLAGS = [
 
 
 def build_id() -> str:
-    """First 16 hex digits of sha256 over the HIP sources and the ABI headers."""
+    """First 16 hex digits of sha256 over the HIP sources and their headers."""
     h = hashlib.sha256()
     for path in (*SRCS, *HEADERS):
         with open(path, "rb") as f:

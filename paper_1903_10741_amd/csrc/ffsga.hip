@@ -36,6 +36,7 @@
 
 #include "ffs_surrogate.h"
 #include "ffsga.h"
+#include "lds_sizes.h"
 
 typedef unsigned long long u64;
 typedef __attribute__((address_space(4))) const int32_t c_i32;
@@ -49,7 +50,8 @@ static __device__ __align__(256) uint8_t scratch[FFS_DECODE_SCRATCH_BYTES];
 
 namespace {
 
-constexpr int kWave = 64;
+using namespace ffs_lds;
+
 constexpr int kMaxGenes = 4096;
 constexpr int kMaxStages = 127;
 constexpr int kDefaultLdsSlots = 4096;
@@ -84,7 +86,6 @@ static_assert(sizeof(Header) <= kHeaderBytes, "header");
 
 enum : int32_t { kErrInval = 1, kErrInfeasible = 2 };
 
-__host__ __device__ constexpr size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // ---------------------------------------------------------------------------
 // Philox4x64-10 (Salmon et al., SC'11): the counter-based generator every GA
@@ -365,37 +366,6 @@ __device__ __forceinline__ int32_t *scratch32(const Lds &l) { return l.rdy; }
 __device__ __forceinline__ uint16_t *scratch16(const Lds &l) { return l.jobs; }
 __device__ __forceinline__ int32_t *scratch32(const LdsN &l) { return (int32_t *)l.jobs; }
 __device__ __forceinline__ uint16_t *scratch16(const LdsN &l) { return l.rdy; }
-
-// Words of one row-ring buffer: a chunk of kWave / o_s ops of o_s words each,
-// plus the record the op loop prefetches one past the chunk (read, never used).
-constexpr int kRing = kWave + 16;
-
-// LDS bytes before the profile region, and in all (cap = 0: no on-chip profile,
-// the region still holds the genes).
-__host__ __device__ inline size_t lds_head(int n) {
-  return align_up((size_t)4 * n + 4, 16) + 2 * align_up((size_t)2 * n + 4, 16) + 4 * kRing;
-}
-__host__ __device__ inline size_t lds_bytes(int n, int cap) {
-  const size_t prof = cap > 0 ? align_up(cap, 16) + kWave : 0, gene = align_up((size_t)4 * n, 16);
-  return lds_head(n) + (prof > gene ? prof : gene);
-}
-// The chip form (LdsN), with room for the wide form of an off-chip redo.
-constexpr int kChipSlots = 32768;
-constexpr int kChipChunk = 16;  // ops whose rows are staged at once
-__host__ __device__ inline size_t lds_head_n(int n, int omp) {
-  return 3 * align_up((size_t)2 * n + 4, 16) + 4 * kChipChunk * omp;
-}
-__host__ __device__ inline size_t lds_bytes_n(int n, int omp, int cap) {
-  const size_t prof = (size_t)3 * kWave + cap, gene = align_up((size_t)4 * n, 16);
-  const size_t chip = lds_head_n(n, omp) + (prof > gene ? prof : gene);
-  const size_t redo = lds_head(n) + gene;
-  return chip > redo ? chip : redo;
-}
-// Whether decode_chip takes a decode: the default rules, and times past the slots
-// still apart from the free time of a lane without a machine.
-__host__ __device__ inline bool chip_rules(int rules, int cap) {
-  return rules == 0 && cap <= kChipSlots;
-}
 
 __device__ __forceinline__ Lds carve_lds(uint8_t *smem, int n) {
   Lds l;
@@ -1745,13 +1715,9 @@ __global__ __launch_bounds__(64) void ga_init_kernel(DInst I, GaDev A, int cap, 
   });
 }
 
-// Row width of the packed table.
-int omp_of(int om) { return om <= 4 ? 4 : om <= 8 ? 8 : 16; }
-
 // LDS of a decode with `cap` on-chip slots in the layout it takes.
 size_t lds_bytes_of(const ffs_instance *in, int cap) {
-  return chip_rules(in->decode_rules, cap) ? lds_bytes_n(in->n_active, omp_of(in->o_max), cap)
-                                           : lds_bytes(in->n_active, cap);
+  return lds_bytes_rules(in->decode_rules, in->n_active, omp_of(in->o_max), cap);
 }
 
 // ---------------------------------------------------------------------------
@@ -3922,11 +3888,8 @@ int batch_cap(const ffs_batch_params *p) {
   return cap > h ? h : cap;
 }
 
-// LDS of a batch's decodes: room for the layouts of both kinds of decode rules.
 size_t batch_lds(const ffs_batch_params *p, int cap) {
-  const size_t wide = lds_bytes(p->max_genes, cap);
-  const size_t chip = cap <= kChipSlots ? lds_bytes_n(p->max_genes, omp_of(p->o_max), cap) : 0;
-  return wide > chip ? wide : chip;
+  return ffs_lds::batch_lds(p->max_genes, omp_of(p->o_max), cap);
 }
 
 BatchArgs batch_args(const ffs_batch *b, const BatchLayout &L) {
@@ -4460,8 +4423,7 @@ int ga_batch_create(ffs_batch *b, const ffs_batch_params *params, void *workspac
   b->omp = omp_of(params->o_max);
   b->workspace = workspace;
   b->workspace_bytes = workspace_bytes;
-  if (lds_bytes(params->max_genes, b->lds_slots) > (size_t)max_lds_bytes())
-    return FFS_E_UNSUPPORTED;
+  if (batch_lds(params, b->lds_slots) > (size_t)max_lds_bytes()) return FFS_E_UNSUPPORTED;
   hipStream_t s = (hipStream_t)stream;
   BatchLayout L = batch_layout(workspace, params);
   if ((rc = clear_header(L.hdr, s))) return rc;
