@@ -3150,43 +3150,21 @@ int compute_units() {
   return v;
 }
 
-// On-chip slots of pop decodes: as asked, or, where the caller leaves them to the
-// library, what resolve_cap takes (the workspace is laid out for that) or as many
-// more as cost no wave. A compute unit has room for 32 waves and needs pop / compute
-// units of them at once, so each may take that share of its LDS, which is given out
-// in pieces of 1280 bytes; past kChipSlots the decoder would be the general one. A
-// schedule that outgrows the slots costs a second decode off chip, four times as
-// long: the plan of an event (one decode of 200 jobs, 10 stages and 4-6 machines,
-// 6400 slots) and its reschedule take 1.90 ms at 4096 slots and 0.75 ms at the 32768
-// that a lone decode gets. Where schedules may well be longer than the slots, 16 of
-// the 32 waves are given up for them (16384 decodes of 50 jobs, 5 stages and 3 machines,
-// where they are not: 380 us a
-// generation on 16 waves, 302 on 32): schedules run 1.5 to
-// 10 times horizon / (stages x machines), the work of a stage spread over its
-// machines, in the random shops of this library, half of them more than 3 times.
-// bytes(cap): LDS of one decode.
-template <class F>
-int roomy_cap(const ffs_instance *in, int32_t lds_slots, int64_t pop, F bytes) {
-  const int base = resolve_cap(in, lds_slots);
-  const int cus = compute_units();
-  if (lds_slots > 0 || base >= in->horizon || cus < 1) return base;
-  const bool lengthy = 6 * (int64_t)in->horizon > (int64_t)base * in->n_stages * in->o_max;
-  const int64_t most = lengthy ? 16 : 32;
-  int64_t waves = (pop + cus - 1) / cus;
-  waves = waves < 1 ? 1 : waves > most ? most : waves;
-  const int64_t room = max_lds_bytes() / waves / 1280 * 1280;
-  int64_t cap = (room - (int64_t)bytes(base) + base) / 64 * 64;
-  const int64_t h = (int64_t)align_up((size_t)in->horizon, 64);
-  if (cap > kChipSlots) cap = kChipSlots;
-  if (cap > h) cap = h;
-  return cap > base ? (int)cap : base;
-}
+// On-chip slots of pop decodes: as asked, or, where the caller leaves them to the library,
+// resolve_cap's or those that cost no wave (roomy_slots). A schedule that outgrows the slots
+// costs a second decode off chip, four times as long: the plan of an event (one decode of 200
+// jobs, 10 stages and 4-6 machines, 6400 slots) and its reschedule take 1.90 ms at 4096 slots
+// and 0.75 ms at the 32768 that a lone decode gets. Waves given up for slots lose more often
+// than they gain: where 16 of a unit's waves were, 8192 FIFO decodes of 70 jobs, 8 stages and
+// 2-3 machines, which fit 4096 slots, took 705 us a generation for 534. Long schedules in
+// large populations are what FFS_LDS_AUTO measures.
 int roomy_cap(const ffs_instance *in, int32_t lds_slots, int64_t pop, bool xy) {
-  if (xy)
-    return roomy_cap(in, lds_slots, pop, [&](int cap) {
-      return lds_bytes_xy(in->n_active, in->n_ops, in->n_stages, in->o_max, cap);
-    });
-  return roomy_cap(in, lds_slots, pop, [&](int cap) { return lds_bytes_of(in, cap); });
+  const int base = resolve_cap(in, lds_slots);
+  if (lds_slots > 0) return base;
+  return roomy_slots(base, in->horizon, pop, compute_units(), max_lds_bytes(), [&](int cap) {
+    return xy ? lds_bytes_xy(in->n_active, in->n_ops, in->n_stages, in->o_max, cap)
+              : lds_bytes_of(in, cap);
+  });
 }
 
 // Bytes of pack_kernel's table: n x g rows of omp words, then n due dates.
