@@ -475,9 +475,11 @@ __device__ __forceinline__ bool live_at(const DInst &I, uint32_t jk, int s, bool
 // once and a ballot marks those that would break the peak; the scalar unit
 // moves the start past the last of them inside the window.
 //
-// RULES: false compiles the default rules only (no per-op rule test);
-// true reads I.rules (FFS_RULE_*). decode_core picks once per decode.
-template <int MAXM, bool PLAN, bool RULES, class Prof>
+// RULES: the decode rules that are compiled, so that the op loop holds no other's code and
+// no per-op test: kDefault, kFifo (FFS_RULE_FIFO alone), kPower (FFS_RULE_POWER_ECT, with or
+// without FIFO, read per stage) or kAnyRules, read from I.rules.
+enum Rules : int { kDefault, kFifo, kPower, kAnyRules };
+template <int MAXM, bool PLAN, int RULES, class Prof>
 __device__ int decode_core_rules(const DInst &I, const Lds &l, Prof &&prof, int64_t *obj_out,
                                  int64_t *work_out, int32_t *start_out, int32_t *mach_out,
                                  int32_t *span_max) {
@@ -527,8 +529,9 @@ __device__ int decode_core_rules(const DInst &I, const Lds &l, Prof &&prof, int6
   prof.order();
 
   const int cap = prof.cap;
-  const bool power_ect = RULES && (I.rules & FFS_RULE_POWER_ECT) != 0;
-  const bool fifo = RULES && (I.rules & FFS_RULE_FIFO) != 0;
+  const bool power_ect =
+      RULES == kPower || (RULES == kAnyRules && (I.rules & FFS_RULE_POWER_ECT) != 0);
+  const bool fifo = RULES == kFifo || (RULES >= kPower && (I.rules & FFS_RULE_FIFO) != 0);
   int64_t work = 0;
   for (int s = 0; s < I.g; ++s) {
     const int os = ld_const(I.nm, s);
@@ -607,13 +610,13 @@ __device__ int decode_core_rules(const DInst &I, const Lds &l, Prof &&prof, int6
     int32_t *rdy_at = l.rdy + opp[0];  // the current op's job
     int rk1 = opp[1];                  // the next op's rank
     int ex = *rdy_at;                  // the current op's job's ready time
-    // The stage's work sum, per lane (summed on the vector unit). Default rules:
+    // The stage's work sum, per lane (summed on the vector unit). Default and FIFO rules:
     // the push-right intervals [t0, t) of one machine's ops are disjoint and lie
     // within the span after RS (< 2^27 slots), so over at most 16 machines they
     // add up to at most 2^31, and the 2p terms to at most 2 * 4096 * 65535 < 2^29:
     // unsigned 32 bits hold the sum. The power-aware rule pushes several machines
     // right per op, over the same slots again for later ops: 64 bits.
-    using StageWork = typename std::conditional<RULES, u64, uint32_t>::type;
+    using StageWork = typename std::conditional<(RULES >= kPower), u64, uint32_t>::type;
     StageWork stage_work = (StageWork)(uint32_t)vz;
     // Each op's profile update is issued by the next op, after its machine choice
     // and before its first profile read: the update's vector work then fills the
@@ -656,10 +659,7 @@ __device__ int decode_core_rules(const DInst &I, const Lds &l, Prof &&prof, int6
         const int first = (int)(kmin & 15u);
         uint32_t best = 0xFFFFFFFFu;
         cw = 3 * os;
-        for (int k = -1; k < os; ++k) {
-          const int m = k < 0 ? first : k;
-          if (k >= 0 && m == first) continue;
-          if ((uint32_t)__builtin_amdgcn_readlane((int)key, m) >= best) continue;
+        auto try_machine = [&](int m) {
           const uint32_t pqm = (uint32_t)__builtin_amdgcn_readlane((int)pqv, m);
           const int pm = word_p(pqm);
           const int t0m = max(ox, __builtin_amdgcn_readlane(fr, m));
@@ -669,6 +669,27 @@ __device__ int decode_core_rules(const DInst &I, const Lds &l, Prof &&prof, int6
           if (km < best) {
             best = km;
             t = tm;
+          }
+        };
+        // The next machine by a ballot over the keys on chip (a lane without a machine is above
+        // any): 530 -> 458 us a generation of 4096 (50 jobs). Off chip, where the redos of a
+        // full chip wait for memory, one after the other: 8192 of 130 jobs 3.8 ms, by the
+        // ballot 4.2.
+        if constexpr (std::decay<decltype(prof)>::type::kLaneAdds) {
+          uint32_t open = ~(1u << first);  // machines still to come
+          for (int m = first;;) {
+            try_machine(m);
+            const uint32_t next = (uint32_t)ballot64(key < best) & open;
+            if (next == 0) break;
+            m = __ffs((int)next) - 1;
+            open &= ~1u << m;
+          }
+        } else {
+          for (int k = -1; k < os; ++k) {
+            const int m = k < 0 ? first : k;
+            if (k >= 0 && m == first) continue;
+            if ((uint32_t)__builtin_amdgcn_readlane((int)key, m) >= best) continue;
+            try_machine(m);
           }
         }
         kmin = best;
@@ -741,16 +762,25 @@ __device__ int decode_core_rules(const DInst &I, const Lds &l, Prof &&prof, int6
   return kDecOk;
 }
 
-template <int MAXM, bool PLAN, class Prof>
+// The decoder that a kernel holds: decode_chip, or the general one under one set of decode
+// rules, each with its off-chip redo; or all of them, picked per decode (a batch's slots
+// differ). One at a time where the host knows which: with all of them in it a generation kernel
+// kept 118 scalars in vector lanes (at most 2 now), and the general decoder lost up to 9 % when
+// decode_chip joined it. A generation of 4096 (50 jobs, 5 stages, 3 machines): FIFO 177 ->
+// 160 us, power-aware 550 -> 458.
+enum Form : int { kChip, kWide, kWideFifo, kWidePower, kAnyForm };
+
+template <int MAXM, bool PLAN, int FORM, class Prof>
 __device__ __forceinline__ int decode_core(const DInst &I, const Lds &l, Prof &&prof,
                                            int64_t *obj_out, int64_t *work_out,
                                            int32_t *start_out, int32_t *mach_out,
                                            int32_t *span_max = nullptr) {
-  if (I.rules == 0)
-    return decode_core_rules<MAXM, PLAN, false>(I, l, prof, obj_out, work_out, start_out, mach_out,
-                                                span_max);
-  return decode_core_rules<MAXM, PLAN, true>(I, l, prof, obj_out, work_out, start_out, mach_out,
-                                             span_max);
+  if (FORM == kAnyForm && I.rules != 0)
+    return decode_core_rules<MAXM, PLAN, kAnyRules>(I, l, prof, obj_out, work_out, start_out,
+                                                    mach_out, span_max);
+  constexpr int R = FORM == kWideFifo ? kFifo : FORM == kWidePower ? kPower : kDefault;
+  return decode_core_rules<MAXM, PLAN, R>(I, l, prof, obj_out, work_out, start_out, mach_out,
+                                          span_max);
 }
 
 // Earliest t >= t0 with every slot of [t, t + p) at most thr (Algorithm 2) over the
@@ -1112,7 +1142,7 @@ __device__ int decode_chip(const DInst &I, const LdsN &l, int cap, int64_t *obj_
   }
   return kDecOk;
 }
-template <int MAXM, bool PLAN>
+template <int MAXM, bool PLAN, int FORM>
 __device__ __forceinline__ int decode_core(const DInst &I, const LdsN &l, const LdsProfile &prof,
                                            int64_t *obj_out, int64_t *work_out,
                                            int32_t *start_out, int32_t *mach_out,
@@ -1121,10 +1151,16 @@ __device__ __forceinline__ int decode_core(const DInst &I, const LdsN &l, const 
 }
 
 // `body` on the LDS layout that a decode with `cap` on-chip slots takes.
-template <class F>
+template <int FORM, class F>
 __device__ __forceinline__ auto in_layout(const DInst &I, int cap, uint8_t *smem, F body) {
-  if (chip_rules(I.rules, cap)) return body(carve_lds_n(smem, I.n, I.omp));
-  return body(carve_lds(smem, I.n));
+  if constexpr (FORM == kChip) {
+    return body(carve_lds_n(smem, I.n, I.omp));
+  } else if constexpr (FORM == kAnyForm) {
+    if (chip_rules(I.rules, cap)) return body(carve_lds_n(smem, I.n, I.omp));
+    return body(carve_lds(smem, I.n));
+  } else {
+    return body(carve_lds(smem, I.n));
+  }
 }
 
 __device__ void flag_error(Header *h, int status) {
@@ -1144,7 +1180,7 @@ __device__ void push_overflow(Header *h, int32_t *list, int idx) {
 // ---------------------------------------------------------------------------
 // Population decode (ffs_decode).
 // ---------------------------------------------------------------------------
-template <int MAXM>
+template <int MAXM, bool PLAN, int FORM>
 __global__ __launch_bounds__(64) void decode_kernel(DInst I, const int32_t *__restrict__ prio,
                                                     int64_t *obj, int64_t *work, int32_t *start,
                                                     int32_t *mach, Header *hdr, int32_t *ovf_list,
@@ -1152,14 +1188,13 @@ __global__ __launch_bounds__(64) void decode_kernel(DInst I, const int32_t *__re
   extern __shared__ __align__(16) uint8_t smem[];
   const int i = blockIdx.x;
   const int32_t *src = prio + (size_t)i * I.n;
-  const size_t plan = (size_t)i * I.n_jobs * I.g;
+  const size_t plan = PLAN ? (size_t)i * I.n_jobs * I.g : 0;
   int64_t *w = work ? work + i : nullptr;
-  const int st = in_layout(I, cap, smem, [&](const auto &l) {
+  const int st = in_layout<FORM>(I, cap, smem, [&](const auto &l) {
     for (int k = __lane_id(); k < I.n; k += kWave) l.gene[k] = src[k];
     __asm__ volatile("" ::: "memory");
     const LdsProfile prof{l.prof, cap};
-    return start ? decode_core<MAXM, true>(I, l, prof, obj + i, w, start + plan, mach + plan)
-                 : decode_core<MAXM, false>(I, l, prof, obj + i, w, nullptr, nullptr);
+    return decode_core<MAXM, PLAN, FORM>(I, l, prof, obj + i, w, start + plan, mach + plan);
   });
   if (st == kDecOk) return;
   if (__lane_id() == 0) obj[i] = -1;
@@ -1188,9 +1223,9 @@ __global__ __launch_bounds__(64) void overflow_kernel(DInst I, const int32_t *__
     const size_t plan = (size_t)i * I.n_jobs * I.g;
     int64_t w = 0;
     int64_t *wp = work ? work + i : &w;
-    const int st = start ? decode_core<MAXM, true>(I, l, prof, obj + i, wp, start + plan, mach + plan,
-                                                   span)
-                         : decode_core<MAXM, false>(I, l, prof, obj + i, wp, nullptr, nullptr, span);
+    const int st =
+        start ? decode_core<MAXM, true, kAnyForm>(I, l, prof, obj + i, wp, start + plan, mach + plan, span)
+              : decode_core<MAXM, false, kAnyForm>(I, l, prof, obj + i, wp, nullptr, nullptr, span);
     if (st == kDecOk && !work && __lane_id() == 0) atomicAdd(&hdr->work, (unsigned long long)w);
     if (st != kDecOk) {
       if (__lane_id() == 0) obj[i] = -1;
@@ -1416,34 +1451,50 @@ __device__ void init_child(const GaDev &A, int n, int i, const L &l) {
 // outcome: the objective, the work count, or an overflow entry `tag` for the
 // off-chip redo, which the wave does itself when it has a profile of its own
 // (in the wide layout, laid over the same LDS: both start at rdy).
-template <int MAXM, class L>
-__device__ void decode_and_record(const DInst &I, const GaDev &A, int i, int cap, const L &l,
-                                  int tag, int32_t *span = nullptr) {
-  int64_t work = 0;
-  int st = decode_core<MAXM, false>(I, l, LdsProfile{l.prof, cap}, A.obj_out + i, &work, nullptr,
-                                    nullptr, span);
+//
+// The GA's arguments are read again after the decode, from the kernel's own (a DInst and
+// then a GaDev, in every kernel that calls this): held across it they take scalar
+// registers that the decoder's searches then keep in vector lanes (a generation of 65536, 200
+// jobs, 10 stages, 4-6 machines, 9.54 ms with 20 of them there, 9.25 with 2).
+typedef __attribute__((address_space(4))) const GaDev c_GaDev;
+template <int MAXM, int FORM, class L>
+__device__ void decode_and_record(const DInst &I, int i, int cap, const L &l, int tag,
+                                  int32_t *span = nullptr) {
+  auto late = []() {
+    auto p = (__attribute__((address_space(4))) const uint8_t *)__builtin_amdgcn_kernarg_segment_ptr();
+    __asm__ volatile("" : "+s"(p));
+    return (c_GaDev *)(p + align_up(sizeof(DInst), alignof(GaDev)));
+  };
+  int64_t work = 0, obj = -1;
+  int st = decode_core<MAXM, false, FORM>(I, l, LdsProfile{l.prof, cap}, &obj, &work, nullptr,
+                                          nullptr, span);
+  c_GaDev *A = late();
   // a schedule longer than the on-chip slots: at least cap + 1 of them
   if (st == kDecOverflow && __lane_id() == 0) {
-    atomicAdd(&A.hdr->overflows, 1ull);
+    atomicAdd(&A->hdr->overflows, 1ull);
     if (span) atomicMax(span, cap + 1);
   }
-  if (st == kDecOverflow && A.redo_prof) {
+  if (st == kDecOverflow && A->redo_prof) {
     const Lds lw = carve_lds((uint8_t *)l.rdy, I.n);
-    const int32_t *src = A.prio_out + (size_t)i * I.n;
+    const int32_t *src = A->prio_out + (size_t)i * I.n;
     for (int k = __lane_id(); k < I.n; k += kWave) lw.gene[k] = src[k];  // this lane's own stores
     __asm__ volatile("" ::: "memory");
     work = 0;
-    const GlobalProfile gp{A.redo_prof + A.redo_stride * i, offchip_cap(I.horizon)};
-    st = decode_core<MAXM, false>(I, lw, gp, A.obj_out + i, &work, nullptr, nullptr, span);
+    const GlobalProfile gp{A->redo_prof + A->redo_stride * i, offchip_cap(I.horizon)};
+    st = decode_core<MAXM, false, FORM>(I, lw, gp, &obj, &work, nullptr, nullptr, span);
     if (st == kDecOverflow) st = kDecInval;  // the horizon bound was wrong: cannot happen
+    A = late();
   }
   if (st == kDecOk) {
-    if (__lane_id() == 0) atomicAdd(&A.hdr->work, (unsigned long long)work);
+    if (__lane_id() == 0) {
+      A->obj_out[i] = obj;
+      atomicAdd(&A->hdr->work, (unsigned long long)work);
+    }
     return;
   }
-  if (__lane_id() == 0) A.obj_out[i] = -1;
-  if (st == kDecOverflow) push_overflow(A.hdr, A.ovf_list, tag);
-  else flag_error(A.hdr, st);
+  if (__lane_id() == 0) A->obj_out[i] = -1;
+  if (st == kDecOverflow) push_overflow(A->hdr, A->ovf_list, tag);
+  else flag_error(A->hdr, st);
 }
 
 template <bool MAX>
@@ -1621,7 +1672,7 @@ __device__ int roulette_spin(const GaDev &A, const u64 *prefix, int pop, int s, 
 
 // Classical GA, one wave per slot: the slot's and its pair partner's parents by
 // roulette, the pair (2k, 2k+1) crossing at slot 2k's cut, swap mutation, decode.
-template <int MAXM>
+template <int MAXM, int FORM>
 __global__ __launch_bounds__(64) void classical_generation_kernel(DInst I, GaDev A, int gen,
                                                                   int cap, const u64 *prefix) {
   extern __shared__ __align__(16) uint8_t smem[];
@@ -1630,16 +1681,16 @@ __global__ __launch_bounds__(64) void classical_generation_kernel(DInst I, GaDev
   const int32_t *other = mine;
   if (partner < pop)
     other = A.prio_in + (size_t)roulette_spin(A, prefix, pop, partner, gen) * I.n;
-  in_layout(I, cap, smem, [&](const auto &l) {
+  in_layout<FORM>(I, cap, smem, [&](const auto &l) {
     build_child(A, I.n, i, gen, l, mine, other, partner < pop ? i & ~1 : -1, 0, true);
-    decode_and_record<MAXM>(I, A, i, cap, l, i);
+    decode_and_record<MAXM, FORM>(I, i, cap, l, i);
   });
 }
 
 // Cellular GA, one wave per cell: the best two of the cell and its four torus
 // neighbours (by objective, then in the order self, up, down, left, right),
 // crossing at the cell's own cut, swap mutation, decode.
-template <int MAXM>
+template <int MAXM, int FORM>
 __global__ __launch_bounds__(64) void cellular_generation_kernel(DInst I, GaDev A, int gen,
                                                                  int cap) {
   extern __shared__ __align__(16) uint8_t smem[];
@@ -1656,10 +1707,10 @@ __global__ __launch_bounds__(64) void cellular_generation_kernel(DInst I, GaDev 
 #pragma unroll
   for (int k = 0; k < 5; ++k)
     if (k != b1 && (b2 < 0 || o[k] < o[b2])) b2 = k;
-  in_layout(I, cap, smem, [&](const auto &l) {
+  in_layout<FORM>(I, cap, smem, [&](const auto &l) {
     build_child(A, I.n, i, gen, l, A.prio_in + (size_t)cand[b1] * I.n,
                 A.prio_in + (size_t)cand[b2] * I.n, i, 0, true);
-    decode_and_record<MAXM>(I, A, i, cap, l, i);
+    decode_and_record<MAXM, FORM>(I, i, cap, l, i);
   });
 }
 
@@ -1691,28 +1742,37 @@ __global__ __launch_bounds__(1024) void elite_update_kernel(const int32_t *prio,
   }
 }
 
-template <int MAXM>
+template <int MAXM, int FORM>
 __global__ __launch_bounds__(64) void ga_generation_kernel(DInst I, GaDev A, int gen, int cap) {
   extern __shared__ __align__(16) uint8_t smem[];
   const int K = A.rows * A.cols;
   const int i = A.isl0 * K + slot_of_block(blockIdx.x, K, A.islands);
-  in_layout(I, cap, smem, [&](const auto &l) {
+  in_layout<FORM>(I, cap, smem, [&](const auto &l) {
     breed_child(A, I.n, i, gen, l);
-    decode_and_record<MAXM>(I, A, i, cap, l, i);
+    decode_and_record<MAXM, FORM>(I, i, cap, l, i);
   });
 }
 
 // Generation 0, individuals from `first` on. span: null, or where the longest schedule
 // is recorded (ga_init sizes the on-chip profile of later generations from it).
-template <int MAXM>
+template <int MAXM, int FORM>
 __global__ __launch_bounds__(64) void ga_init_kernel(DInst I, GaDev A, int cap, int32_t *span,
                                                      int first) {
   extern __shared__ __align__(16) uint8_t smem[];
   const int i = first + blockIdx.x;
-  in_layout(I, cap, smem, [&](const auto &l) {
+  in_layout<FORM>(I, cap, smem, [&](const auto &l) {
     init_child(A, I.n, i, l);
-    decode_and_record<MAXM>(I, A, i, cap, l, i, span);
+    decode_and_record<MAXM, FORM>(I, i, cap, l, i, span);
   });
+}
+
+// f(the form, as a constant) for the decoder that a decode with `cap` on-chip slots takes.
+template <class F>
+auto by_form(const ffs_instance *in, int cap, F f) {
+  if (chip_rules(in->decode_rules, cap)) return f(std::integral_constant<int, kChip>());
+  if (in->decode_rules & FFS_RULE_POWER_ECT) return f(std::integral_constant<int, kWidePower>());
+  if (in->decode_rules & FFS_RULE_FIFO) return f(std::integral_constant<int, kWideFifo>());
+  return f(std::integral_constant<int, kWide>());
 }
 
 // LDS of a decode with `cap` on-chip slots in the layout it takes.
@@ -2329,7 +2389,7 @@ __global__ __launch_bounds__(kScoreWaves *kWave) void sg_score_block_kernel(
 
 // Screened generation: every cell breeds V candidate children, keeps the one
 // with the lowest surrogate score (lowest v on ties), stores and decodes it.
-template <int MAXM>
+template <int MAXM, int FORM>
 __global__ __launch_bounds__(64) void ga_screened_kernel(DInst I, GaDev A, int gen, int cap,
                                                          const float *table, const float *theta,
                                                          int V, float *scores, int32_t *choice,
@@ -2337,7 +2397,7 @@ __global__ __launch_bounds__(64) void ga_screened_kernel(DInst I, GaDev A, int g
   extern __shared__ __align__(16) uint8_t smem[];
   const int K = A.rows * A.cols;
   const int i = A.isl0 * K + slot_of_block(blockIdx.x, K, A.islands);
-  in_layout(I, cap, smem, [&](const auto &l) {
+  in_layout<FORM>(I, cap, smem, [&](const auto &l) {
     const float b3 = theta[FFS_SG_PARAMS - 1];
     int best = 0;
     float best_s = 0.f;
@@ -2353,7 +2413,7 @@ __global__ __launch_bounds__(64) void ga_screened_kernel(DInst I, GaDev A, int g
     }
     if (choice && __lane_id() == 0) choice[i] = best;
     breed_child(A, I.n, i, gen, l, best, true);
-    decode_and_record<MAXM>(I, A, i, cap, l, i);
+    decode_and_record<MAXM, FORM>(I, i, cap, l, i);
   });
 }
 
@@ -2577,15 +2637,16 @@ template <int MAXM, class L>
 __device__ void decode_slot(const DInst &I, const GaDev &A, int i, int cap, const L &l,
                             const GlobalProfile &gp, int32_t *span_max = nullptr) {
   int64_t work = 0;
-  int st = decode_core<MAXM, false>(I, l, LdsProfile{l.prof, cap}, A.obj_out + i, &work, nullptr,
-                                    nullptr, span_max);
+  int st = decode_core<MAXM, false, kAnyForm>(I, l, LdsProfile{l.prof, cap}, A.obj_out + i, &work,
+                                              nullptr, nullptr, span_max);
   if (st == kDecOverflow) {
     const Lds lw = carve_lds((uint8_t *)l.rdy, I.n);  // both layouts start at rdy
     const int32_t *src = A.prio_out + (size_t)i * I.n;
     for (int k = __lane_id(); k < I.n; k += kWave) lw.gene[k] = src[k];
     __asm__ volatile("" ::: "memory");
     work = 0;
-    st = decode_core<MAXM, false>(I, lw, gp, A.obj_out + i, &work, nullptr, nullptr, span_max);
+    st = decode_core<MAXM, false, kAnyForm>(I, lw, gp, A.obj_out + i, &work, nullptr, nullptr,
+                                            span_max);
   }
   if (st == kDecOk) {
     if (__lane_id() == 0) atomicAdd(&A.hdr->work, (unsigned long long)work);
@@ -2613,7 +2674,7 @@ __global__ __launch_bounds__(64) void batch_generation_kernel(BatchArgs B, int c
     const GaDev A = slot_ga(S, B, gen);
     const GlobalProfile gp{gp_mem, offchip_cap(S.I.horizon)};
     const int first = ISLAND ? item % per_slot * K : item % per_slot;
-    in_layout(S.I, S.cap, smem, [&](const auto &l) {
+    in_layout<kAnyForm>(S.I, S.cap, smem, [&](const auto &l) {
       for (int i = first; i < first + (ISLAND ? K : 1); ++i) {
         breed_child(A, S.I.n, i, gen, l);
         decode_slot<MAXM>(S.I, A, i, S.cap, l, gp);
@@ -2633,7 +2694,7 @@ __global__ __launch_bounds__(64) void batch_init_kernel(BatchArgs B, int d) {
   A0.prio_out = S.prio[0];
   A0.obj_out = S.obj[0];
   const GlobalProfile gp{B.gprof + B.gstride * blockIdx.x, offchip_cap(S.I.horizon)};
-  in_layout(S.I, S.cap, smem, [&](const auto &l) {
+  in_layout<kAnyForm>(S.I, S.cap, smem, [&](const auto &l) {
     for (int i = blockIdx.x; i < B.pop; i += gridDim.x) {
       init_child(A0, S.I.n, i, l);
       decode_slot<MAXM>(S.I, A0, i, S.cap, l, gp, &B.slots[d].span);
@@ -3213,8 +3274,11 @@ int run_decode(const ffs_instance *in, const int32_t *prio, int32_t pop, int64_t
                hipStream_t stream) {
   const DInst d = make_dinst(in, L.pq);
   const size_t shmem = lds_bytes_of(in, cap);
-  hipError_t e = launch(0, decode_kernel<MAXM>, dim3(pop), dim3(kWave), shmem, stream, d, prio, obj,
-                        work, start, mach, L.hdr, L.ovf_list, cap);
+  hipError_t e = by_form(in, cap, [&](auto form) {
+    return launch(0, start ? decode_kernel<MAXM, true, form()> : decode_kernel<MAXM, false, form()>,
+                  dim3(pop), dim3(kWave), shmem, stream, d, prio, obj, work, start, mach, L.hdr,
+                  L.ovf_list, cap);
+  });
   if (e != hipSuccess) return FFS_E_DEVICE;
   if (cap < in->horizon) {
     e = launch(3, overflow_kernel<MAXM>, dim3(kFixBlocks), dim3(kWave), lds_bytes(in->n_active, 0),
@@ -3438,16 +3502,19 @@ int build_xy_table(const ffs_instance *in, int32_t *op, int32_t *g0, hipStream_t
              : FFS_E_DEVICE;
 }
 
-// Single-wave workgroups of the generation kernel that one compute unit holds at
-// `bytes` of LDS each (the runtime's occupancy figure: LDS granularity,
+// Single-wave workgroups of the generation kernel that one compute unit holds with
+// `cap` on-chip slots each (the runtime's occupancy figure: LDS granularity,
 // registers and wave slots included); 0 if the runtime cannot say.
 template <int MAXM>
-int waves_per_cu(size_t bytes) {
-  int b = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, (const void *)ga_generation_kernel<MAXM>,
-                                                   kWave, bytes) != hipSuccess)
-    return 0;
-  return b;
+int waves_per_cu(const ffs_instance *in, int cap) {
+  return by_form(in, cap, [&](auto form) {
+    int b = 0;
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(
+               &b, (const void *)ga_generation_kernel<MAXM, form()>, kWave, lds_bytes_of(in, cap)) ==
+                   hipSuccess
+               ? b
+               : 0;
+  });
 }
 
 // Threads of a block that goes once over K objectives: enough waves to have them all
@@ -3473,11 +3540,11 @@ int ga_init_impl(ffs_ga *ga, const ffs_instance *in, const GaLayout &L, hipStrea
     const int64_t len = host.span_max, top = probe_cap(in, kAutoSlots);
     int64_t lo = (int64_t)align_up((size_t)(len + len / 64 + 64), 64);
     if (lo > top) lo = top;
-    const int w = waves_per_cu<MAXM>(lds_bytes_of(in, (int)lo));
+    const int w = waves_per_cu<MAXM>(in, (int)lo);
     int64_t a = lo / 64, b = top / 64;  // waves_per_cu falls as the slots grow
     while (w > 0 && a < b) {
       const int64_t m = (a + b + 1) / 2;
-      if (waves_per_cu<MAXM>(lds_bytes_of(in, (int)(m * 64))) >= w)
+      if (waves_per_cu<MAXM>(in, (int)(m * 64)) >= w)
         a = m;
       else
         b = m - 1;
@@ -3497,20 +3564,22 @@ int ga_init_impl(ffs_ga *ga, const ffs_instance *in, const GaLayout &L, hipStrea
     // population of more than kSizing waves a unit decodes that many with them, and
     // the rest with the slots that those take: 65536 individuals of 200 jobs, 10
     // stages, 4-6 machines take 8.3 ms (16 waves a unit) instead of 13.9 (8).
+    auto generate = [&](int count, int slots, int first) {
+      return by_form(in, slots, [&](auto form) {
+        return launch(1, ga_init_kernel<MAXM, form()>, dim3(count), dim3(kWave),
+                      lds_bytes_of(in, slots), stream, d, A, slots, span, first);
+      });
+    };
     constexpr int kSizing = 4;
     const int part = auto_cap ? kSizing * compute_units() : 0;
     int cap0 = cap, done = 0;
     if (part > 0 && pop > 2 * part) {
-      if (launch(1, ga_init_kernel<MAXM>, dim3(part), dim3(kWave), lds_bytes_of(in, cap), stream, d,
-                 A, cap, span, 0) != hipSuccess)
-        return FFS_E_DEVICE;
+      if (generate(part, cap, 0) != hipSuccess) return FFS_E_DEVICE;
       if ((rc = ga_overflow<MAXM>(in, L, 0, cap, stream, false, span))) return rc;
       if ((rc = size_slots(&cap0))) return rc;
       done = part;
     }
-    if (launch(1, ga_init_kernel<MAXM>, dim3(pop - done), dim3(kWave), lds_bytes_of(in, cap0), stream,
-               d, A, cap0, span, done) != hipSuccess)
-      return FFS_E_DEVICE;
+    if (generate(pop - done, cap0, done) != hipSuccess) return FFS_E_DEVICE;
     if ((rc = ga_overflow<MAXM>(in, L, 0, cap0, stream, false, span))) return rc;
   }
   if (launch(-1, elite_init_kernel, dim3(ga->params.islands), block_of(K), 0, stream,
@@ -3643,10 +3712,14 @@ int ga_step_groups(ffs_ga *ga, const ffs_instance *in, const GaLayout &L, int32_
       A.islands = i1 - i0;
       const dim3 grid((unsigned)((i1 - i0) * K));
       const hipError_t e =
-          scr ? launch(5, ga_screened_kernel<MAXM>, grid, dim3(kWave), shmem, sg, d, A, gen, cap,
-                       scr->table, scr->theta, scr->variants, scr->scores, scr->choice, ga->pop)
-          : xy ? launch(1, ga_generation_xy_kernel, grid, dim3(kWave), shmem, sg, d, T, A, gen, cap)
-               : launch(1, ga_generation_kernel<MAXM>, grid, dim3(kWave), shmem, sg, d, A, gen, cap);
+          xy ? launch(1, ga_generation_xy_kernel, grid, dim3(kWave), shmem, sg, d, T, A, gen, cap)
+             : by_form(in, cap, [&](auto form) {
+                 return scr ? launch(5, ga_screened_kernel<MAXM, form()>, grid, dim3(kWave), shmem, sg,
+                                     d, A, gen, cap, scr->table, scr->theta, scr->variants,
+                                     scr->scores, scr->choice, ga->pop)
+                            : launch(1, ga_generation_kernel<MAXM, form()>, grid, dim3(kWave), shmem,
+                                     sg, d, A, gen, cap);
+               });
       ok = e == hipSuccess &&
            launch(2, replace_wave_kernel, dim3(i1 - i0), dim3(kWave), 0, sg,
                   L.prio[1 - cur] + (size_t)i0 * K * n, L.obj[1 - cur] + (size_t)i0 * K,
@@ -3699,20 +3772,25 @@ int ga_step_impl(ffs_ga *ga, const ffs_instance *in, int32_t n_gen, hipStream_t 
       if (launch(-1, fitness_scan_kernel, dim3(1), dim3(1024), 0, stream,
                  (const int64_t *)A.obj_in, pop, (const Header *)L.hdr, L.prefix) != hipSuccess)
         return FFS_E_DEVICE;
-      e = launch(1, classical_generation_kernel<MAXM>, dim3(pop), dim3(kWave), shmem, stream, d, A,
-                 gen, cap, (const u64 *)L.prefix);
-    } else if (scheme == FFS_GA_CELLULAR) {
-      e = launch(1, cellular_generation_kernel<MAXM>, dim3(pop), dim3(kWave), shmem, stream, d, A,
-                 gen, cap);
-    } else if (scr)
-      e = launch(5, ga_screened_kernel<MAXM>, dim3(pop), dim3(kWave), shmem, stream, d, A, gen, cap,
-                 scr->table, scr->theta, scr->variants, scr->scores, scr->choice, pop);
-    else if (xy)
+    }
+    if (xy)
       e = launch(1, ga_generation_xy_kernel, dim3(pop), dim3(kWave), shmem, stream, d, T, A, gen,
                  cap);
     else
-      e = launch(1, ga_generation_kernel<MAXM>, dim3(pop), dim3(kWave), shmem, stream, d, A,
-                 gen, cap);
+      e = by_form(in, cap, [&](auto form) {
+        const dim3 grid(pop), block(kWave);
+        if (scheme == FFS_GA_CLASSICAL)
+          return launch(1, classical_generation_kernel<MAXM, form()>, grid, block, shmem, stream, d, A,
+                        gen, cap, (const u64 *)L.prefix);
+        if (scheme == FFS_GA_CELLULAR)
+          return launch(1, cellular_generation_kernel<MAXM, form()>, grid, block, shmem, stream, d, A,
+                        gen, cap);
+        if (scr)
+          return launch(5, ga_screened_kernel<MAXM, form()>, grid, block, shmem, stream, d, A, gen,
+                        cap, scr->table, scr->theta, scr->variants, scr->scores, scr->choice, pop);
+        return launch(1, ga_generation_kernel<MAXM, form()>, grid, block, shmem, stream, d, A, gen,
+                      cap);
+      });
     if (e != hipSuccess) return FFS_E_DEVICE;
     int rc = ga_overflow<MAXM>(in, L, 1 - cur, cap, stream, xy);
     if (rc) return rc;
@@ -3746,34 +3824,31 @@ int ga_step_impl(ffs_ga *ga, const ffs_instance *in, int32_t n_gen, hipStream_t 
   return FFS_OK;
 }
 
+template <int MAXM, int FORM>
+void set_lds_limits_of(int lim) {
+  for (const void *k :
+       {(const void *)decode_kernel<MAXM, false, FORM>, (const void *)decode_kernel<MAXM, true, FORM>,
+        (const void *)ga_generation_kernel<MAXM, FORM>, (const void *)ga_init_kernel<MAXM, FORM>,
+        (const void *)ga_screened_kernel<MAXM, FORM>,
+        (const void *)classical_generation_kernel<MAXM, FORM>,
+        (const void *)cellular_generation_kernel<MAXM, FORM>})
+    (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, lim);
+}
+
 template <int MAXM>
 void set_lds_limits() {
   static bool done = false;
   if (done) return;
   done = true;
   const int lim = max_lds_bytes();
-  (void)hipFuncSetAttribute((const void *)decode_kernel<MAXM>,
-                      hipFuncAttributeMaxDynamicSharedMemorySize, lim);
-  (void)hipFuncSetAttribute((const void *)overflow_kernel<MAXM>,
-                      hipFuncAttributeMaxDynamicSharedMemorySize, lim);
-  (void)hipFuncSetAttribute((const void *)ga_generation_kernel<MAXM>,
-                      hipFuncAttributeMaxDynamicSharedMemorySize, lim);
-  (void)hipFuncSetAttribute((const void *)ga_init_kernel<MAXM>,
-                      hipFuncAttributeMaxDynamicSharedMemorySize, lim);
-  (void)hipFuncSetAttribute((const void *)ga_screened_kernel<MAXM>,
-                      hipFuncAttributeMaxDynamicSharedMemorySize, lim);
-  (void)hipFuncSetAttribute((const void *)classical_generation_kernel<MAXM>,
-                      hipFuncAttributeMaxDynamicSharedMemorySize, lim);
-  (void)hipFuncSetAttribute((const void *)cellular_generation_kernel<MAXM>,
-                      hipFuncAttributeMaxDynamicSharedMemorySize, lim);
-  (void)hipFuncSetAttribute((const void *)decode_xy_kernel<MAXM>,
-                      hipFuncAttributeMaxDynamicSharedMemorySize, lim);
-  (void)hipFuncSetAttribute((const void *)overflow_xy_kernel<MAXM>,
-                      hipFuncAttributeMaxDynamicSharedMemorySize, lim);
-  (void)hipFuncSetAttribute((const void *)ga_init_xy_kernel,
-                      hipFuncAttributeMaxDynamicSharedMemorySize, lim);
-  (void)hipFuncSetAttribute((const void *)ga_generation_xy_kernel,
-                      hipFuncAttributeMaxDynamicSharedMemorySize, lim);
+  set_lds_limits_of<MAXM, kChip>(lim);
+  set_lds_limits_of<MAXM, kWide>(lim);
+  set_lds_limits_of<MAXM, kWideFifo>(lim);
+  set_lds_limits_of<MAXM, kWidePower>(lim);
+  for (const void *k : {(const void *)overflow_kernel<MAXM>, (const void *)decode_xy_kernel<MAXM>,
+                        (const void *)overflow_xy_kernel<MAXM>, (const void *)ga_init_xy_kernel,
+                        (const void *)ga_generation_xy_kernel})
+    (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, lim);
 }
 
 // ---------------------------------------------------------------------------
