@@ -3219,10 +3219,10 @@ int compute_units() {
 // than they gain: where 16 of a unit's waves were, 8192 FIFO decodes of 70 jobs, 8 stages and
 // 2-3 machines, which fit 4096 slots, took 705 us a generation for 534. Long schedules in
 // large populations are what FFS_LDS_AUTO measures.
-int roomy_cap(const ffs_instance *in, int32_t lds_slots, int64_t pop, bool xy) {
+int roomy_cap(const ffs_instance *in, int32_t lds_slots, int64_t pop, bool xy, bool groups) {
   const int base = resolve_cap(in, lds_slots);
   if (lds_slots > 0) return base;
-  return roomy_slots(base, in->horizon, pop, compute_units(), max_lds_bytes(), [&](int cap) {
+  return roomy_slots(base, in->horizon, pop, groups, compute_units(), max_lds_bytes(), [&](int cap) {
     return xy ? lds_bytes_xy(in->n_active, in->n_ops, in->n_stages, in->o_max, cap)
               : lds_bytes_of(in, cap);
   });
@@ -4061,7 +4061,7 @@ int decode_job_vectors(const ffs_instance *inst, const int32_t *prio, int32_t po
     return rc;
   }
   if ((rc = pack(inst, L.pq, s))) return rc;
-  cap = roomy_cap(inst, lds_slots, pop, false);
+  cap = roomy_cap(inst, lds_slots, pop, false, false);
   switch (omp_of(inst->o_max)) {
     case 4:
       set_lds_limits<4>();
@@ -4237,7 +4237,7 @@ int ffs_decode_xy(const ffs_instance *inst, const int32_t *genes, int32_t pop, i
   if ((rc = clear_header(L.hdr, s))) return rc;
   if ((rc = pack(inst, L.pq, s))) return rc;
   if ((rc = build_xy_table(inst, L.xyop, L.xyg0, s))) return rc;
-  cap = roomy_cap(inst, lds_slots, pop, true);
+  cap = roomy_cap(inst, lds_slots, pop, true, false);
   switch (omp_of(inst->o_max)) {
     case 4:
       set_lds_limits<4>();
@@ -4292,7 +4292,8 @@ int ga_init(ffs_ga *ga, const ffs_instance *inst, const ffs_ga_params *params, u
   ga->params = *params;
   ga->n_genes = (int32_t)chrom_len(inst, params);
   ga->pop = params->islands * params->rows * params->cols;
-  if (!auto_cap) cap = roomy_cap(inst, params->lds_slots, ga->pop, params->encoding == 1);
+  if (!auto_cap)
+    cap = roomy_cap(inst, params->lds_slots, ga->pop, params->encoding == 1, params->islands > 1);
   ga->seed = seed;
   ga->shop = shop;
   ga->event = event;

@@ -58,18 +58,19 @@ constexpr int64_t waves_held(size_t bytes, int64_t lds) {
 
 // On-chip slots of pop decodes whose caller leaves them to the library: base (what the
 // workspace is laid out for), or as many more as leave each of `cus` compute units room for as
-// many waves as it holds at base and the population can use. One wave a unit is left over:
-// island groups do not spread evenly (37 islands of 110 decodes, 50 jobs, on exactly the 16
-// waves a unit that they need: 97.7 us a generation; at 4096 slots, 93.4). Less than half of
-// base more is not taken unless no schedule can be longer: a schedule that outgrows both is
-// found out later (8192 decodes of 130 jobs, 8 stages and 2 machines under the power-aware rule:
-// 4.65 ms a generation at 4928 slots, 4.34 at 4096). Past kChipSlots the decoder would be the
-// general one. bytes(cap): LDS of one decode.
+// many waves as it holds at base and the population can use. With `groups`, the launches of
+// island groups, one wave a unit is left over: they do not spread evenly (37 islands of 110
+// decodes, 50 jobs, on exactly the 16 waves a unit that they need: 97.7 us a generation; at
+// 4096 slots, 93.4). Less than half of base more is not taken unless no schedule can be longer:
+// a schedule that outgrows both is found out later (8192 decodes of 130 jobs, 8 stages and 2
+// machines under the power-aware rule: 4.65 ms a generation at 4928 slots, 4.34 at 4096). Past
+// kChipSlots the decoder would be the general one. bytes(cap): LDS of one decode.
 template <class F>
-int roomy_slots(int base, int64_t horizon, int64_t pop, int64_t cus, int64_t lds, F bytes) {
+int roomy_slots(int base, int64_t horizon, int64_t pop, bool groups, int64_t cus, int64_t lds,
+                F bytes) {
   if (base >= horizon || cus < 1) return base;
   const int64_t held = waves_held(bytes(base), lds);
-  int64_t waves = (pop + cus - 1) / cus + 1;
+  int64_t waves = (pop + cus - 1) / cus + groups;
   if (waves > held) waves = held;
   if (waves < 1) return base;
   const int64_t room = lds / waves / 1280 * 1280, h = (int64_t)align_up((size_t)horizon, 64);

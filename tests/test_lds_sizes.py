@@ -64,13 +64,14 @@ int main() {
     for (int n : {1, 20, 50, 116, 200, 385, 1000, 4096})
       for (int omp : {4, 8, 16})
         for (int64_t horizon : {5000, 8543, 20229, 35868, 400000})
-          for (int64_t pop : {1, 2, 255, 256, 257, 1024, 4070, 4096, 4097, 4300, 6000, 8192, 16384, 65536}) {
+          for (int64_t pop : {1, 2, 255, 256, 257, 1024, 4070, 4096, 4097, 4300, 6000, 8192, 16384, 65536})
+          for (bool groups : {false, true}) {
             const int base = 4096;
             auto bytes = [&](int cap) { return ffs_lds::lds_bytes_rules(rules, n, omp, cap); };
-            const int cap = ffs_lds::roomy_slots(base, horizon, pop, cus, lds, bytes);
-            // waves that a unit can use: its share of the population and one more, since launches
-            // of island groups do not spread evenly
-            const int64_t use = (pop + cus - 1) / cus + 1;
+            const int cap = ffs_lds::roomy_slots(base, horizon, pop, groups, cus, lds, bytes);
+            // waves that a unit can use: its share of the population, and one more for island
+            // groups, whose launches do not spread evenly
+            const int64_t use = (pop + cus - 1) / cus + groups;
             int64_t want = ffs_lds::waves_held(bytes(base), lds);
             if (want > use) want = use;
             const int64_t got = ffs_lds::waves_held(bytes(cap), lds);
