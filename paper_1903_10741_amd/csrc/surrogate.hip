@@ -315,11 +315,13 @@ __global__ __launch_bounds__(256) void train_fwd_kernel(const float *theta, cons
 // sums its run of consecutive entries [g0 + t*c, g0 + (t+1)*c) in index order,
 // c = ceil(group / 256), and the 256 partial sums are added by a fixed pairwise tree,
 // so every run gives the same bits. The logarithms, the larger part of the work, are
-// taken once each by all 1024 threads and kept in LDS where the group fits (`logs`
-// holds it); a larger group takes them again in each of the three passes. 4096
-// entries: 20.7 -> 10.5 us.
+// taken once each by all 1024 threads and kept in LDS where the group fits (`logs`, the
+// 64 KB that a kernel's own arrays may take less the sums; two blocks of 1024 threads
+// fill a compute unit anyway); a larger group takes them again in each of the three
+// passes. 4096 entries: 20.7 -> 10.5 us; with its launches, 7456: 31.7 -> 16.1.
 // ---------------------------------------------------------------------------
-constexpr int kTargetThreads = 1024, kTargetSums = 256, kTargetLogs = 4096;
+constexpr int kTargetThreads = 1024, kTargetSums = 256;
+constexpr int kTargetLogs = (65536 - kTargetSums * 8) / 8 / 17 * 16;  // 7456, one in 17 left out
 __device__ __forceinline__ double block_sum_fixed(double v, double *buf) {
   const int t = threadIdx.x;
   if (t < kTargetSums) buf[t] = v;
