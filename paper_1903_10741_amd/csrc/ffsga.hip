@@ -417,7 +417,7 @@ __device__ __forceinline__ uint32_t machine_min_scalar(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_readlane((int)machine_min<MAXM>(v), MAXM - 1);
 }
 
-// Minimum, or OR, over each group of MAXM neighbouring lanes, left in all of them
+// Minimum over each group of MAXM neighbouring lanes, left in all of them
 // (quad permutes, then the half row and the row mirrored).
 template <int CTRL>
 __device__ __forceinline__ uint32_t dpp(uint32_t v) {
@@ -431,15 +431,6 @@ __device__ __forceinline__ uint32_t group_min(uint32_t v) {
   if (MAXM > 8) v = min(v, dpp<0x140>(v));
   return v;
 }
-template <int MAXM>
-__device__ __forceinline__ uint32_t group_or(uint32_t v) {
-  v |= dpp<0xB1>(v);
-  v |= dpp<0x4E>(v);
-  if (MAXM > 4) v |= dpp<0x141>(v);
-  if (MAXM > 8) v |= dpp<0x140>(v);
-  return v;
-}
-
 __device__ __forceinline__ int64_t wave_sum64(int64_t v) {
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, kWave);
@@ -3561,9 +3552,9 @@ int ga_init_impl(ffs_ga *ga, const ffs_instance *in, const GaLayout &L, hipStrea
     if ((rc = ga_overflow<MAXM>(in, L, 0, cap, stream, true))) return rc;
   } else {
     // The sizing decode's slots leave a compute unit room for few waves. So a
-    // population of more than kSizing waves a unit decodes that many with them, and
-    // the rest with the slots that those take: 65536 individuals of 200 jobs, 10
-    // stages, 4-6 machines take 8.3 ms (16 waves a unit) instead of 13.9 (8).
+    // population of more than twice kSizing waves a unit decodes kSizing waves a unit
+    // with them, and the rest with the slots that those take: 65536 individuals of 200
+    // jobs, 10 stages, 4-6 machines take 8.3 ms (16 waves a unit) instead of 13.9 (8).
     auto generate = [&](int count, int slots, int first) {
       return by_form(in, slots, [&](auto form) {
         return launch(1, ga_init_kernel<MAXM, form()>, dim3(count), dim3(kWave),
