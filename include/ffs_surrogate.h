@@ -107,9 +107,9 @@ size_t sg_train_workspace_size(int32_t n_genes, int32_t batch);
  * loss (device float32 [1], may be NULL) receives the batch loss before the
  * step; grad (device float32 [FFS_SG_PARAMS], may be NULL) the gradient.
  * A batch holding a gene outside 1..n or a target that is not finite is found on the
- * device: the step then leaves the parameters and moments unchanged and the
- * next ffs_status(workspace) returns FFS_E_INVAL (model->step still counts
- * the call). The workspace starts with the 256-byte status block ffs_status
+ * device: the step then leaves the parameters, moments, loss and grad
+ * unchanged and the next ffs_status(workspace) returns FFS_E_INVAL
+ * (model->step still counts the call). The workspace starts with the 256-byte status block ffs_status
  * reads; its status is cleared at the start of every step.
  * Errors: FFS_E_INVAL, FFS_E_WORKSPACE, FFS_E_DEVICE. */
 int sg_train_step(ffs_surrogate *model, const float *feats, int32_t n_genes, const int32_t *prio,
