@@ -2596,10 +2596,11 @@ __device__ __forceinline__ T ld_const_struct(const T *p) {
 
 __device__ __forceinline__ GaDev slot_ga(const BatchSlot &S, const BatchArgs &B, int gen) {
   GaDev A;
-  A.prio_in = S.prio[(gen - 1) & 1];
-  A.obj_in = S.obj[(gen - 1) & 1];
-  A.prio_out = S.prio[gen & 1];
-  A.obj_out = S.obj[gen & 1];
+  const bool odd = gen & 1;  // (selects: an index would put the struct in memory)
+  A.prio_in = odd ? S.prio[0] : S.prio[1];
+  A.obj_in = odd ? S.obj[0] : S.obj[1];
+  A.prio_out = odd ? S.prio[1] : S.prio[0];
+  A.obj_out = odd ? S.obj[1] : S.obj[0];
   A.elite = S.elite;
   A.elite_obj = S.elite_obj;
   A.stage_prio = S.stage_prio;
@@ -2621,30 +2622,45 @@ __device__ __forceinline__ GaDev slot_ga(const BatchSlot &S, const BatchArgs &B,
   return A;
 }
 
-// Decode the child in l.gene (already stored in A.prio_out) with the on-chip
+// A slot as it is now, read again: what is read before a decode and used after it would
+// take scalar registers from the decoder (decode_and_record). By its registers a compute
+// unit holds 28 waves of a batch's generation for the 20 before (12 with island items);
+// 32 shops of 20 to 60 jobs, 16 waves a unit, 971 -> 874 us a generation.
+__device__ __forceinline__ BatchSlot slot_again(const BatchSlot *p) {
+  __asm__ volatile("" : "+s"(p));
+  return ld_const_struct(p);
+}
+
+// Decode the child in l.gene (already stored in the slot's prio[side]) with the on-chip
 // profile; a decode that outgrows it is redone at once with this block's
 // off-chip profile.
 template <int MAXM, class L>
-__device__ void decode_slot(const DInst &I, const GaDev &A, int i, int cap, const L &l,
-                            const GlobalProfile &gp, int32_t *span_max = nullptr) {
-  int64_t work = 0;
-  int st = decode_core<MAXM, false, kAnyForm>(I, l, LdsProfile{l.prof, cap}, A.obj_out + i, &work,
-                                              nullptr, nullptr, span_max);
+__device__ void decode_slot(const BatchSlot *slot, int side, const BatchArgs &B, int i, const L &l,
+                            int32_t *span_max = nullptr) {
+  int64_t work = 0, obj = -1;
+  int st;
+  {
+    const BatchSlot S = slot_again(slot);
+    st = decode_core<MAXM, false, kAnyForm>(S.I, l, LdsProfile{l.prof, S.cap}, &obj, &work, nullptr,
+                                            nullptr, span_max);
+  }
   if (st == kDecOverflow) {
-    const Lds lw = carve_lds((uint8_t *)l.rdy, I.n);  // both layouts start at rdy
-    const int32_t *src = A.prio_out + (size_t)i * I.n;
-    for (int k = __lane_id(); k < I.n; k += kWave) lw.gene[k] = src[k];
+    const BatchSlot S = slot_again(slot);
+    const Lds lw = carve_lds((uint8_t *)l.rdy, S.I.n);  // both layouts start at rdy
+    const int32_t *src = (side ? S.prio[1] : S.prio[0]) + (size_t)i * S.I.n;
+    for (int k = __lane_id(); k < S.I.n; k += kWave) lw.gene[k] = src[k];
     __asm__ volatile("" ::: "memory");
     work = 0;
-    st = decode_core<MAXM, false, kAnyForm>(I, lw, gp, A.obj_out + i, &work, nullptr, nullptr,
-                                            span_max);
+    const GlobalProfile gp{B.gprof + B.gstride * blockIdx.x, offchip_cap(S.I.horizon)};
+    st = decode_core<MAXM, false, kAnyForm>(S.I, lw, gp, &obj, &work, nullptr, nullptr, span_max);
   }
+  const BatchSlot S = slot_again(slot);
+  if (__lane_id() == 0) (side ? S.obj[1] : S.obj[0])[i] = st == kDecOk ? obj : -1;
   if (st == kDecOk) {
-    if (__lane_id() == 0) atomicAdd(&A.hdr->work, (unsigned long long)work);
+    if (__lane_id() == 0) atomicAdd(&B.hdr->work, (unsigned long long)work);
     return;
   }
-  if (__lane_id() == 0) A.obj_out[i] = -1;
-  flag_error(A.hdr, st == kDecOverflow ? kDecInval : st);
+  flag_error(B.hdr, st == kDecOverflow ? kDecInval : st);
 }
 
 // (value, index) argmin / argmax over one wave, lowest index on ties.
@@ -2656,22 +2672,24 @@ __global__ __launch_bounds__(64) void batch_generation_kernel(BatchArgs B, int c
   const int K = B.rows * B.cols;
   const int per_slot = ISLAND ? B.islands : B.pop;
   const int total = B.n_slots * per_slot;
-  uint8_t *gp_mem = B.gprof + B.gstride * blockIdx.x;
   for (int item = blockIdx.x; item < total; item += gridDim.x) {
-    const int d = item / per_slot;
-    const BatchSlot S = ld_const_struct(B.slots + d);
+    const BatchSlot *slot = B.slots + item / per_slot;
+    const BatchSlot S = ld_const_struct(slot);
     if (!S.active || S.cls != cls) continue;
-    const int gen = S.gen + 1;
-    const GaDev A = slot_ga(S, B, gen);
-    const GlobalProfile gp{gp_mem, offchip_cap(S.I.horizon)};
     const int first = ISLAND ? item % per_slot * K : item % per_slot;
     in_layout<kAnyForm>(S.I, S.cap, smem, [&](const auto &l) {
       for (int i = first; i < first + (ISLAND ? K : 1); ++i) {
-        breed_child(A, S.I.n, i, gen, l);
-        decode_slot<MAXM>(S.I, A, i, S.cap, l, gp);
+        {
+          const BatchSlot T = slot_again(slot);
+          breed_child(slot_ga(T, B, T.gen + 1), T.I.n, i, T.gen + 1, l);
+        }
+        decode_slot<MAXM>(slot, (S.gen + 1) & 1, B, i, l);
       }
     });
-    if (ISLAND) replace_island_wave(A, item % per_slot, K, S.I.n);
+    if (ISLAND) {
+      const BatchSlot T = slot_again(slot);
+      replace_island_wave(slot_ga(T, B, T.gen + 1), item % per_slot, K, T.I.n);
+    }
   }
 }
 
@@ -2679,16 +2697,16 @@ __global__ __launch_bounds__(64) void batch_generation_kernel(BatchArgs B, int c
 template <int MAXM>
 __global__ __launch_bounds__(64) void batch_init_kernel(BatchArgs B, int d) {
   extern __shared__ __align__(16) uint8_t smem[];
-  const BatchSlot S = ld_const_struct(B.slots + d);
-  const GaDev A = slot_ga(S, B, 1);  // generation 0 goes to prio[0]: the "input" side of 1
-  GaDev A0 = A;
-  A0.prio_out = S.prio[0];
-  A0.obj_out = S.obj[0];
-  const GlobalProfile gp{B.gprof + B.gstride * blockIdx.x, offchip_cap(S.I.horizon)};
+  BatchSlot *slot = B.slots + d;
+  const BatchSlot S = ld_const_struct(slot);
   in_layout<kAnyForm>(S.I, S.cap, smem, [&](const auto &l) {
     for (int i = blockIdx.x; i < B.pop; i += gridDim.x) {
-      init_child(A0, S.I.n, i, l);
-      decode_slot<MAXM>(S.I, A0, i, S.cap, l, gp, &B.slots[d].span);
+      {
+        const BatchSlot T = slot_again(slot);
+        // generation 0 goes to prio[0], the output of a generation of even number
+        init_child(slot_ga(T, B, 0), T.I.n, i, l);
+      }
+      decode_slot<MAXM>(slot, 0, B, i, l, &slot->span);
     }
   });
 }
