@@ -221,8 +221,9 @@ typedef struct {
  * gets FFS_E_UNSUPPORTED): ga_init decodes generation 0 with as many on-chip
  * slots as one workgroup's LDS holds (at most 16384, no more than the horizon
  * needs; a longer schedule is redone off chip) and records the longest schedule
- * (end - RS); of a population much larger than the chip holds at once it decodes a
- * first part so and the rest with the slots that part takes. Every later generation
+ * (end - RS); where those slots leave a compute unit fewer than 16 waves and the
+ * population has more than 16 for each, it decodes a first part so and the rest with
+ * the slots that part takes. Every later generation
  * keeps that schedule plus 1/64 of it and 64 slots on chip, widened to the
  * most slots (a multiple of 64, at most 32768) at which a compute
  * unit still holds as many waves of the generation kernel (the runtime's

@@ -3588,10 +3588,13 @@ int ga_init_impl(ffs_ga *ga, const ffs_instance *in, const GaLayout &L, hipStrea
       return FFS_E_DEVICE;
     if ((rc = ga_overflow<MAXM>(in, L, 0, cap, stream, true))) return rc;
   } else {
-    // The sizing decode's slots leave a compute unit room for few waves. So a
-    // population of more than twice kSizing waves a unit decodes kSizing waves a unit
-    // with them, and the rest with the slots that those take: 65536 individuals of 200
-    // jobs, 10 stages, 4-6 machines take 8.3 ms (16 waves a unit) instead of 13.9 (8).
+    // The sizing decode's slots may leave a compute unit room for few waves. Where that
+    // is fewer than 16, a population of more than 16 waves a unit decodes kSizing a
+    // unit with them, and the rest with the slots that those take: 65536 individuals of
+    // 200 jobs, 10 stages, 4-6 machines (9 waves with the sizing slots) take 8.3 ms
+    // instead of 13.9. The first part and reading its span cost a decode's chain and 30
+    // us: 2176 individuals of 50 jobs (17 waves) 226 us in two parts, 151 in one; 5120
+    // of 117 jobs (13 waves) 498 and 564, 3072 of them 437 and 405.
     auto generate = [&](int count, int slots, int first) {
       return by_form(in, slots, [&](auto form) {
         return launch(1, ga_init_kernel<MAXM, form()>, dim3(count), dim3(kWave),
@@ -3599,9 +3602,9 @@ int ga_init_impl(ffs_ga *ga, const ffs_instance *in, const GaLayout &L, hipStrea
       });
     };
     constexpr int kSizing = 4;
-    const int part = auto_cap ? kSizing * compute_units() : 0;
+    const int cus = auto_cap ? compute_units() : 0, part = kSizing * cus;
     int cap0 = cap, done = 0;
-    if (part > 0 && pop > 2 * part) {
+    if (cus > 0 && pop > 16 * cus && waves_held(lds_bytes_of(in, cap), max_lds_bytes()) < 16) {
       if (generate(part, cap, 0) != hipSuccess) return FFS_E_DEVICE;
       if ((rc = ga_overflow<MAXM>(in, L, 0, cap, stream, false, span))) return rc;
       if ((rc = size_slots(&cap0))) return rc;
