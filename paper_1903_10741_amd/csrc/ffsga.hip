@@ -2645,35 +2645,37 @@ __device__ __forceinline__ GaDev slot_ga(const BatchSlot &S, const BatchArgs &B,
 // take scalar registers from the decoder (decode_and_record). By its registers a compute
 // unit holds 28 waves of a batch's generation for the 20 before (12 with island items);
 // 32 shops of 20 to 60 jobs, 16 waves a unit, 971 -> 874 us a generation.
+template <bool AGAIN = true>
 __device__ __forceinline__ BatchSlot slot_again(const BatchSlot *p) {
-  __asm__ volatile("" : "+s"(p));
+  if (AGAIN) __asm__ volatile("" : "+s"(p));
   return ld_const_struct(p);
 }
 
 // Decode the child in l.gene (already stored in the slot's prio[side]) with the on-chip
 // profile; a decode that outgrows it is redone at once with this block's
-// off-chip profile.
-template <int MAXM, class L>
+// off-chip profile. FORM: the decoder (kAnyForm: the slot's); AGAIN: whether the slot is
+// read again.
+template <int MAXM, int FORM, bool AGAIN, class L>
 __device__ void decode_slot(const BatchSlot *slot, int side, const BatchArgs &B, int i, const L &l,
                             int32_t *span_max = nullptr) {
   int64_t work = 0, obj = -1;
   int st;
   {
-    const BatchSlot S = slot_again(slot);
-    st = decode_core<MAXM, false, kAnyForm>(S.I, l, LdsProfile{l.prof, S.cap}, &obj, &work, nullptr,
-                                            nullptr, span_max);
+    const BatchSlot S = slot_again<AGAIN>(slot);
+    st = decode_core<MAXM, false, FORM>(S.I, l, LdsProfile{l.prof, S.cap}, &obj, &work, nullptr,
+                                        nullptr, span_max);
   }
   if (st == kDecOverflow) {
-    const BatchSlot S = slot_again(slot);
+    const BatchSlot S = slot_again<AGAIN>(slot);
     const Lds lw = carve_lds((uint8_t *)l.rdy, S.I.n);  // both layouts start at rdy
     const int32_t *src = (side ? S.prio[1] : S.prio[0]) + (size_t)i * S.I.n;
     for (int k = __lane_id(); k < S.I.n; k += kWave) lw.gene[k] = src[k];
     __asm__ volatile("" ::: "memory");
     work = 0;
     const GlobalProfile gp{B.gprof + B.gstride * blockIdx.x, offchip_cap(S.I.horizon)};
-    st = decode_core<MAXM, false, kAnyForm>(S.I, lw, gp, &obj, &work, nullptr, nullptr, span_max);
+    st = decode_core<MAXM, false, FORM>(S.I, lw, gp, &obj, &work, nullptr, nullptr, span_max);
   }
-  const BatchSlot S = slot_again(slot);
+  const BatchSlot S = slot_again<AGAIN>(slot);
   if (__lane_id() == 0) (side ? S.obj[1] : S.obj[0])[i] = st == kDecOk ? obj : -1;
   if (st == kDecOk) {
     if (__lane_id() == 0) atomicAdd(&B.hdr->work, (unsigned long long)work);
@@ -2702,7 +2704,7 @@ __global__ __launch_bounds__(64) void batch_generation_kernel(BatchArgs B, int c
           const BatchSlot T = slot_again(slot);
           breed_child(slot_ga(T, B, T.gen + 1), T.I.n, i, T.gen + 1, l);
         }
-        decode_slot<MAXM>(slot, (S.gen + 1) & 1, B, i, l);
+        decode_slot<MAXM, kAnyForm, true>(slot, (S.gen + 1) & 1, B, i, l);
       }
     });
     if (ISLAND) {
@@ -2712,20 +2714,18 @@ __global__ __launch_bounds__(64) void batch_generation_kernel(BatchArgs B, int c
   }
 }
 
-// Generation 0 of slot d.
-template <int MAXM>
+// Generation 0 of slot d. One launch a slot, so the host picks the decoder; a block has a
+// child or two, too few to read the slot again for.
+template <int MAXM, int FORM>
 __global__ __launch_bounds__(64) void batch_init_kernel(BatchArgs B, int d) {
   extern __shared__ __align__(16) uint8_t smem[];
   BatchSlot *slot = B.slots + d;
   const BatchSlot S = ld_const_struct(slot);
-  in_layout<kAnyForm>(S.I, S.cap, smem, [&](const auto &l) {
+  in_layout<FORM>(S.I, S.cap, smem, [&](const auto &l) {
     for (int i = blockIdx.x; i < B.pop; i += gridDim.x) {
-      {
-        const BatchSlot T = slot_again(slot);
-        // generation 0 goes to prio[0], the output of a generation of even number
-        init_child(slot_ga(T, B, 0), T.I.n, i, l);
-      }
-      decode_slot<MAXM>(slot, 0, B, i, l, &slot->span);
+      // generation 0 goes to prio[0], the output of a generation of even number
+      init_child(slot_ga(S, B, 0), S.I.n, i, l);
+      decode_slot<MAXM, FORM, false>(slot, 0, B, i, l, &slot->span);
     }
   });
 }
@@ -4041,18 +4041,22 @@ void set_batch_lds_limits() {
                             hipFuncAttributeMaxDynamicSharedMemorySize, lim);
   (void)hipFuncSetAttribute((const void *)batch_generation_kernel<MAXM, false>,
                             hipFuncAttributeMaxDynamicSharedMemorySize, lim);
-  (void)hipFuncSetAttribute((const void *)batch_init_kernel<MAXM>,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, lim);
+  for (const void *k : {(const void *)batch_init_kernel<MAXM, kChip>, (const void *)batch_init_kernel<MAXM, kWide>,
+                        (const void *)batch_init_kernel<MAXM, kWideFifo>,
+                        (const void *)batch_init_kernel<MAXM, kWidePower>})
+    (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, lim);
 }
 
 template <int MAXM>
-int batch_init_launch(const ffs_batch *b, const BatchArgs &B, int slot, const BatchLayout &L,
-                      hipStream_t s) {
+int batch_init_launch(const ffs_batch *b, const BatchArgs &B, int slot, const ffs_instance *inst,
+                      int cap, const BatchLayout &L, hipStream_t s) {
   set_batch_lds_limits<MAXM>();
   const ffs_batch_params &p = b->params;
   const size_t shmem = batch_lds(&p, b->lds_slots);
   const int grid = b->pop < b->blocks ? b->pop : b->blocks;
-  if (launch(-1, batch_init_kernel<MAXM>, dim3(grid), dim3(kWave), shmem, s, B, slot) != hipSuccess ||
+  if (by_form(inst, cap, [&](auto form) {
+        return launch(-1, batch_init_kernel<MAXM, form()>, dim3(grid), dim3(kWave), shmem, s, B, slot);
+      }) != hipSuccess ||
       launch(-1, batch_class_kernel, dim3(1), dim3(kWave), 0, s, B, slot, batch_classes(&p),
              b->lds_slots) != hipSuccess)
     return FFS_E_DEVICE;
@@ -4571,9 +4575,9 @@ int ga_batch_set(ffs_batch *b, int32_t slot, const ffs_instance *inst, uint64_t 
   }
   const BatchArgs B = batch_args(b, L);
   switch (b->omp) {
-    case 4: return batch_init_launch<4>(b, B, slot, L, s);
-    case 8: return batch_init_launch<8>(b, B, slot, L, s);
-    default: return batch_init_launch<16>(b, B, slot, L, s);
+    case 4: return batch_init_launch<4>(b, B, slot, inst, S.cap, L, s);
+    case 8: return batch_init_launch<8>(b, B, slot, inst, S.cap, L, s);
+    default: return batch_init_launch<16>(b, B, slot, inst, S.cap, L, s);
   }
 }
 
