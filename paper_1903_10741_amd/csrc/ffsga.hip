@@ -1463,13 +1463,13 @@ __device__ void init_child(const GaDev &A, int n, int i, const L &l) {
 // (in the wide layout, laid over the same LDS: both start at rdy).
 //
 // The GA's arguments are read again after the decode, from the kernel's own (a DInst and
-// then a GaDev, in every kernel that calls this): held across it they take scalar
+// then a GaDev, in every kernel that this is inlined into): held across it they take scalar
 // registers that the decoder's searches then keep in vector lanes (a generation of 65536, 200
 // jobs, 10 stages, 4-6 machines, 9.54 ms with 20 of them there, 9.25 with 2).
 typedef __attribute__((address_space(4))) const GaDev c_GaDev;
 template <int MAXM, int FORM, class L>
-__device__ void decode_and_record(const DInst &I, int i, int cap, const L &l, int tag,
-                                  int32_t *span = nullptr) {
+__device__ __forceinline__ void decode_and_record(const DInst &I, int i, int cap, const L &l,
+                                                  int tag, int32_t *span = nullptr) {
   auto late = []() {
     auto p = (__attribute__((address_space(4))) const uint8_t *)__builtin_amdgcn_kernarg_segment_ptr();
     __asm__ volatile("" : "+s"(p));
@@ -4041,9 +4041,10 @@ void set_batch_lds_limits() {
                             hipFuncAttributeMaxDynamicSharedMemorySize, lim);
   (void)hipFuncSetAttribute((const void *)batch_generation_kernel<MAXM, false>,
                             hipFuncAttributeMaxDynamicSharedMemorySize, lim);
-  for (const void *k : {(const void *)batch_init_kernel<MAXM, kChip>, (const void *)batch_init_kernel<MAXM, kWide>,
-                        (const void *)batch_init_kernel<MAXM, kWideFifo>,
-                        (const void *)batch_init_kernel<MAXM, kWidePower>})
+  for (const void *k :
+       {(const void *)batch_init_kernel<MAXM, kChip>, (const void *)batch_init_kernel<MAXM, kWide>,
+        (const void *)batch_init_kernel<MAXM, kWideFifo>,
+        (const void *)batch_init_kernel<MAXM, kWidePower>})
     (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, lim);
 }
 
