@@ -1016,9 +1016,14 @@ __device__ int decode_chip(const DInst &I, const LdsN &l, int cap, int64_t *obj_
     if (!have) load_rows(s, 0, cnt);
     int gene = l.op[min(lane & (C - 1), cnt - 1)];  // lane k < C: op k of the chunk
     int ready = l.rdy[gene];
-    int64_t delay = 0;
     uint32_t psum = 0;
-    const int all = cnt;
+    work += (int64_t)3 * os * cnt;
+    // The ops whose pushes go straight to the search (below): the first ones of a stage,
+    // unless it and the one before are passed within a few rows, by 24 jobs or by 32 on many
+    // machines. A generation of 288, those ops walking and searching at once: 17 jobs on
+    // 8-12 machines a stage 54 and 69 us, 28 jobs 79 and 90; 28 jobs on 3-5 machines 64 and
+    // 61, 50 jobs on 8 120 and 114.
+    const int firsts = cnt > min(max(4 * os, 24), 32) ? os : 0;
     for (int base = 0; base < cnt; base += C) {
 #pragma unroll
       for (int i = 0; i < NR; ++i) l.rec[i * kWave + lane] = row[i];
@@ -1080,12 +1085,12 @@ __device__ int decode_chip(const DInst &I, const LdsN &l, int cap, int64_t *obj_
               e += h.move;
               if (__builtin_expect(!h.ok, 0)) {
                 // Further: a stage's first ops, which start under the peak of the stage
-                // before, go past most of it, and are searched for at once. Of the
-                // others nine in ten end within the next row or two, which cost a hop
-                // each: the search alone took 100 us a generation of 256 (82 jobs, 3
-                // stages, 2-3 machines, a fifth of the ops pushed 65 to 131 slots), with
-                // two rows walked first 75; 65536 of 200 jobs 9.2 -> 8.7 ms.
-                int walks = base + k < os ? 0 : 2;
+                // before, go past most of it, and are searched for at once unless it is
+                // short. Of the others nine in ten end within the next row or two, which
+                // cost a hop each: the search alone took 100 us a generation of 256 (82
+                // jobs, 3 stages, 2-3 machines, a fifth of the ops pushed 65 to 131
+                // slots), with two rows walked first 75; 65536 of 200 jobs 9.2 -> 8.7 ms.
+                int walks = base + k < firsts ? 0 : 2;
                 for (; walks > 0; --walks) {
                   at = ends_at + min(e, cap + kWave);
                   const uint32_t v2 = at[kWave];
@@ -1108,7 +1113,7 @@ __device__ int decode_chip(const DInst &I, const LdsN &l, int cap, int64_t *obj_
           sk += (e - e0) << kKeyBits;
           fr = win ? (uint32_t)sk & ~dlow : fr;
           ends = ffs_writelane(sk, k, ends);
-          delay += e - e0;
+          work += e - e0;
         }
         w = w_next;
       }
@@ -1129,7 +1134,6 @@ __device__ int decode_chip(const DInst &I, const LdsN &l, int cap, int64_t *obj_
       ready = ready_n;
     }
     psum_all += psum;
-    work += delay + (int64_t)3 * os * all;
   }
   if (over) return kDecOverflow;
   work += 2 * wave_sum64((int64_t)psum_all);
